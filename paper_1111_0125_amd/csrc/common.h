@@ -133,21 +133,23 @@ inline size_t spinor_rhs_bytes(int prec, size_t Vh) {
 // hop 2*mu   : L = eta_mu(x) U_mu(x)                     applied to chi(x + mu)
 // hop 2*mu+1 : L = -(eta_mu(x - mu) U_mu(x - mu))^dagger applied to chi(x - mu)
 // so the Dirac operator is a plain sum of eight matrix-vector products.
-// The 72 complex entries (hop-major, then row-major 3x3) are stored word-major
-// over the sites so that a wavefront reading word w of 64 consecutive sites
-// touches one contiguous span:
-//   P64   72 words of double2 (one complex)      at [w][Vh]
-//   P32   36 words of float4  (two complex)      at [w][Vh]
-//   P16S  36 words of uint2   (two half2 complex)at [w][Vh], plus one fp32
-//         scale per site at [Vh] (largest |Re|,|Im| over the 144 reals).
-// Hop pair mu (hops 2mu, 2mu+1) is 18 complex = words 18mu.. (P64) or 9mu..
-// (P32, P16S).
+// The 72 complex entries (hop-major, then row-major 3x3) are stored in tiles
+// of 64 consecutive output sites, word-major inside a tile ([tile][word][64],
+// the last tile padded), so that a wavefront's links are one contiguous run
+// that it reads in order:
+//   P64   72 words of double2 (one complex)
+//   P32   36 words of float4  (two complex)
+//   P16S  per hop pair 4 words of uint4 (four half2 complex) and one of uint2
+//         (two), plus one fp32 scale per site at [Vh] (largest |Re|,|Im|
+//         over the 144 reals).
+// Hop pair mu (hops 2mu, 2mu+1) is 18 complex: a run of link_pair_bytes per
+// site inside the tile. Stored [word][Vh] over the whole lattice instead, a
+// wavefront touches as many places a lattice apart as it has words.
 // ---------------------------------------------------------------------------
 // 12-parameter storage (SU(3) links): per output site and hop pair mu, the
 // first two rows of U_mu(x) then of U_mu(x - mu)^dagger (12 complex, no
-// phases): P64 48 words of double2, P32 24 words of float4, P16S 24 words of
-// uint2 at [w][Vh] plus the site scale of the full form; pair mu is words
-// 12mu.. (P64) or 6mu.. (P32, P16S). The kernels rebuild
+// phases): P64 48 words of double2, P32 24 words of float4, P16S 12 words of
+// uint4 in the same tiles plus the site scale of the full form. The kernels rebuild
 // each third row as the conjugated cross product of the first two and apply
 // +eta_mu(x) to the forward and -eta_mu(x) to the backward link
 // (eta_mu(x - mu) = eta_mu(x): the phase depends on the coordinates before mu).
@@ -157,17 +159,16 @@ inline size_t spinor_rhs_bytes(int prec, size_t Vh) {
 // three-hop pair
 // hop 8+2mu  : L = eta_mu(x) N_mu(x)                       applied to chi(x + 3mu)
 // hop 9+2mu  : L = -(eta_mu(x - 3mu) N_mu(x - 3mu))^dagger applied to chi(x - 3mu)
-// in the same word-major layout (P64 144 words, P32 / P16S 72 words; the
-// P16S scale covers all 288 reals). Always the full 18-parameter form:
-// fat and long links are not unitary.
-inline size_t link_bytes(int prec, size_t Vh, bool r12 = false, int npairs = 4) {
-    const size_t k = (size_t)npairs / 4;
-    if (prec == P64) return k * Vh * (r12 ? 48 : 72) * 16;
-    if (prec == P32) return k * Vh * (r12 ? 24 : 36) * 16;
-    return k * Vh * (r12 ? 24 : 36) * 8;
+// in the same layout (the P16S scale covers all 288 reals). Always the full
+// 18-parameter form: fat and long links are not unitary.
+constexpr uint32_t kLinkTile = 64;  // sites per tile
+// Bytes of one hop pair of one site.
+__host__ __device__ constexpr uint32_t link_pair_bytes(int prec, bool r12) {
+    return (r12 ? 12u : 18u) * (prec == P64 ? 16u : prec == P32 ? 8u : 4u);
 }
-inline size_t gauge_parity_bytes(int prec, size_t Vh, bool r12 = false, int npairs = 4) {
-    return link_bytes(prec, Vh, r12, npairs) + (prec == P16S ? Vh * 4 : 0);
+inline size_t link_bytes(int prec, size_t Vh, bool r12 = false, int npairs = 4) {
+    const size_t tiles = (Vh + kLinkTile - 1) / kLinkTile;
+    return tiles * kLinkTile * (size_t)npairs * link_pair_bytes(prec, r12);
 }
 
 // ---------------------------------------------------------------------------

@@ -15,6 +15,8 @@
 //
 // This file is compiled once per storage precision (HOP_PREC) and pair
 // count (HOP_NP).
+#include <type_traits>
+
 #include "kern.h"
 #include "launch.h"
 
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(kBlock) void k_hop(HopArgs a) {
             }
             static_for<0, PB>([&](auto kc) {
                 constexpr int k = decltype(kc)::value;
-                load_pair_raw<P, NT>(a.gauge, a.gscale, Vh, s, j * B + k, r12, pl[k]);
+                load_pair_raw<P, NT, NP>(a.gauge, a.gscale, s, j * B + k, r12, pl[k]);
             });
         }
         if (a.st && a.fin.partials) {
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(kBlock) void k_hop(HopArgs a) {
                     load_raw<P>(a, (const char*)a.in, 0, nf, lazy_nb, wfk);
                     load_raw<P>(a, (const char*)a.in, 0, nb, lazy_nb, wbk);
                 }
-                load_pair<P, NT>(a.gauge, a.gscale, Vh, s, mu, r12, eta_sign(mu & 3, x, y, z), lr, li, ps);
+                load_pair<P, NT, NP>(a.gauge, a.gscale, s, mu, r12, eta_sign(mu & 3, x, y, z), lr, li, ps);
             }
 #pragma unroll
             for (int r = 0; r < N; ++r) {
@@ -398,6 +400,240 @@ __global__ __launch_bounds__(kBlock) void k_hop(HopArgs a) {
     }
 }
 
+// ------------------------------------------------------------------ one right-hand side
+
+// Load a colour vector from field f (a kernel argument, so uniform): the
+// plane's address stays in scalar registers and the site is a 32-bit offset
+// to it (sites per parity below kHop1MaxSites).
+template <int P>
+__device__ __forceinline__ void load_site32(const void* f, uint32_t Vh, uint32_t s,
+                                            typename Real<P>::T (&re)[3],
+                                            typename Real<P>::T (&im)[3]) {
+    if constexpr (P == P16S) {
+        f16s_decode(*(const u4v*)((const char*)f + s * 16u), re, im);
+    } else {
+        using V = std::conditional_t<P == P64, d2v, f2v>;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const V v = *(const V*)((const char*)f + (size_t)c * Vh * sizeof(V) + s * (uint32_t)sizeof(V));
+            re[c] = v.x;
+            im[c] = v.y;
+        }
+    }
+}
+
+// Everything one hop pair reads: links, both neighbours, and with a deferred
+// direction their residuals.
+template <int P, bool LAZY>
+struct PairIn {
+    using T = typename Real<P>::T;
+    PairRaw<P> l;
+    T fr[3], fi[3], br[3], bi[3];
+    T gr[LAZY ? 3 : 1], gi[LAZY ? 3 : 1], hr[LAZY ? 3 : 1], hi[LAZY ? 3 : 1];
+};
+
+// The hop stages of one right-hand side with S lanes per site (four hop pairs
+// per lane), the link form and the deferred direction fixed at compile time.
+// Bound by the links' memory traffic: what matters is how many loads a wave
+// keeps in flight against how many waves fit, so the request of a pair's
+// operands runs a fixed number of pairs ahead of its products. Measured on
+// A at 32^3 x 64 (us, full / 12-parameter links; improved operator at
+// 24^3 x 48): fp64 with 1, 2, 3 pairs ahead 427 / 311, 427 / 310, 436 / 340 (289,
+// 285, 293), fp16+scale 120 / 91, 117 / 88, 119 / 90, fp32 235 / 170, 232 / 165,
+// 231 / 165 and with all four 225 / 160 (141 improved). The kernel
+// before it, k_hop below with its choices at run time (both link forms formed
+// and selected, third rows rebuilt for full links too): 446 / 329 (309), 127 /
+// 100 and 232 / 161 (150).
+template <int P, int S, int EPI, int NP, bool R12, bool LAZY, bool FIN>
+__global__ __launch_bounds__(kBlock) void k_hop1(HopArgs a) {
+    constexpr int B = NP / S;
+    constexpr int D = P == P32 ? 4 : 2;             // pairs requested ahead
+    static_assert(D <= B, "pairs ahead");
+    constexpr bool LNB = LAZY && EPI == EPI_PLAIN;  // direction formed at the neighbours
+    using T = typename Real<P>::T;
+    const uint32_t blk = logical_block(a.swizzle, a.tile_bps);
+    const uint32_t gt = blk * kBlock + threadIdx.x;
+    const uint32_t s = gt / S;
+    const int j = (int)(gt % S);
+    const uint32_t Vh = a.g.Vh;
+    const bool valid = s < Vh;
+    const uint32_t sl = valid ? s : Vh - 1;  // lanes past the end repeat the last site
+    int x, y, z, t;
+    site_coords(a.g, sl, a.p_out, x, y, z, t);
+    // Requests that run behind products: all neighbour indices first, because
+    // their selects compile to branches, and requests and products only keep
+    // their order inside one basic block. All requests up front: each pair's
+    // indices with its request (fewer registers).
+    uint32_t nf[B], nb[B];
+    auto indices = [&](int k) { pair_neighbours<NP>(a.g, sl, x, y, z, t, j * B + k, nf[k], nb[k]); };
+    if constexpr (D < B) static_for<0, B>([&](auto kc) { indices(decltype(kc)::value); });
+    PairIn<P, LNB> q[D];
+    auto request = [&](int k, PairIn<P, LNB>& w) {
+        const int mu = j * B + k;
+        if constexpr (D == B) indices(k);
+        load_site32<P>(a.in, Vh, nf[k], w.fr, w.fi);
+        load_site32<P>(a.in, Vh, nb[k], w.br, w.bi);
+        if constexpr (LNB) {
+            load_site32<P>(a.lazy_r, Vh, nf[k], w.gr, w.gi);
+            load_site32<P>(a.lazy_r, Vh, nb[k], w.hr, w.hi);
+        }
+        load_pair_raw<P, true, NP>(a.gauge, a.gscale, sl, mu, R12, w.l);
+    };
+    static_for<0, D>([&](auto kc) { request(decltype(kc)::value, q[decltype(kc)::value]); });
+    T xr[3], xi[3], rr[3], ri[3];
+    if constexpr (EPI != EPI_PLAIN) {
+        load_site32<P>(a.x, Vh, sl, xr, xi);
+        if constexpr (LAZY) load_site32<P>(a.lazy_r, Vh, sl, rr, ri);
+    }
+    // the state: finalised here from the previous reduction's partials (FIN),
+    // else only the three values that the stage uses
+    bool act = true;
+    double beta = 0.0, mm = a.m2[0];
+    if constexpr (FIN) {
+        RhsState s1 = *a.st;
+        Reduce F = a.fin;
+        F.st = a.st;
+        finalize_wave1(F, a.run_mask, s1);
+        act = (s1.flags & a.run_mask) != 0;
+        beta = s1.beta;
+        mm = s1.m2;
+    } else {
+        const RhsState* st = a.st ? a.st : &kNoState;
+        act = !a.st || (st->flags & a.run_mask);
+        if (a.st) {
+            beta = st->beta;
+            mm = st->m2;
+        }
+    }
+    const T be = (T)beta;
+    auto direction = [&](T (&vr)[3], T (&vi)[3], const T* gr, const T* gi) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            vr[c] = fma(be, vr[c], gr[c]);
+            vi[c] = fma(be, vi[c], gi[c]);
+        }
+        round_site<P>(vr, vi);
+    };
+    double dv[1] = {0.0};
+    if (act) {
+        T pdr[4][3], pdi[4][3], ar[3], ai[3];
+        static_for<0, B>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            PairIn<P, LNB>& w = q[k % D];
+            T lr[18], li[18], pr[3], pi[3];
+            PairScale<T> ps;
+            finish_pair<P>(R12, eta_sign((j * B + k) & 3, x, y, z), w.l, lr, li, ps);
+            if constexpr (LNB) {
+                direction(w.fr, w.fi, w.gr, w.gi);
+                direction(w.br, w.bi, w.hr, w.hi);
+            }
+            pair_start(lr, li, w.fr, w.fi, pr, pi);
+            pair_finish(lr, li, ps, w.br, w.bi, pr, pi);
+            // the next request stays behind this pair's products, which the
+            // compiler would otherwise hold back until every link of the site
+            // has been loaded (an empty statement that uses them)
+            if constexpr (k + D < B) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) asm volatile("" : "+v"(pr[c]), "+v"(pi[c])::"memory");
+            }
+            // the balanced tree ((p0 + p1) + (p2 + p3)) + ...
+            constexpr int lvl = (k & 1) == 0 ? 0 : (k & 2) == 0 ? 1 : (k & 4) == 0 ? 2 : 3;
+#pragma unroll
+            for (int l = 0; l < lvl; ++l)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    pr[c] = pdr[l][c] + pr[c];
+                    pi[c] = pdi[l][c] + pi[c];
+                }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if constexpr (k == B - 1) {
+                    ar[c] = pr[c];
+                    ai[c] = pi[c];
+                } else {
+                    pdr[lvl][c] = pr[c];
+                    pdi[lvl][c] = pi[c];
+                }
+            }
+            if constexpr (k + D < B) request(k + D, q[k % D]);
+        });
+        if constexpr (S > 1) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int off = 1; off < S; off <<= 1) {
+                    ar[c] = ar[c] + __shfl_xor(ar[c], off, 64);
+                    ai[c] = ai[c] + __shfl_xor(ai[c], off, 64);
+                }
+        }
+        if (valid && j == 0) {
+            if constexpr (EPI == EPI_PLAIN) {
+                store_site<P>(a.out, Vh, s, ar, ai);
+            } else {
+                if constexpr (LAZY) {
+                    direction(xr, xi, rr, ri);
+                    store_site<P>((void*)a.x, Vh, s, xr, xi);
+                }
+                const T m2 = (T)mm;
+                T hr[3], hi[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    hr[c] = fma(m2, xr[c], -ar[c]);
+                    hi[c] = fma(m2, xi[c], -ai[c]);
+                }
+                store_site<P>(a.out, Vh, s, hr, hi);
+                if constexpr (EPI == EPI_XPAY_DOT) {
+                    double acc = 0.0;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        acc = fma((double)xr[c], (double)hr[c], acc);
+                        acc = fma((double)xi[c], (double)hi[c], acc);
+                    }
+                    dv[0] = acc;
+                }
+            }
+        }
+    }
+    if constexpr (EPI == EPI_XPAY_DOT) block_chunk_partials<1, S>(dv, a.red, blk);
+}
+
+// k_hop1 serves the default launch shape (non-temporal link loads, four pairs
+// per lane) of the iteration and operator kernels; the other shapes and the
+// fp64 fix-ups, which gather x + y or are gated, take k_hop. Its 32-bit
+// offsets hold planes of at most 4 GiB (16 bytes a site).
+// fp32 with Eq.5's four pairs keeps k_hop too: there k_hop1 gained 3 % on A with
+// full links at 32^3 x 64 (225 against 232 us), nothing with 12-parameter links
+// (160 us), and whole solves became slower (16^3 x 32 27.1 against 25.4 ms,
+// 24^3 x 48 full 136.5 against 134.7 ms).
+constexpr uint32_t kHop1MaxSites = 1u << 27;
+template <int P, int NP>
+constexpr bool kUseHop1 = P != P32 || NP == 8;
+
+template <int P, int S, int EPI, bool R12, bool LAZY>
+static hipError_t run_hop1(const HopArgs& a, const Issue& is) {
+    HopArgs arg = a;
+    void* args[] = {&arg};
+    const void* f = reinterpret_cast<const void*>(&k_hop1<P, S, EPI, HOP_NP, R12, LAZY, false>);
+    if constexpr (EPI == EPI_PLAIN && LAZY)
+        if (a.fin.partials) f = reinterpret_cast<const void*>(&k_hop1<P, S, EPI, HOP_NP, R12, LAZY, true>);
+    return issue_kernel(is, f, hop_blocks(a.g.Vh, S), kBlock, args);
+}
+
+template <int P, int EPI>
+static hipError_t dispatch_hop1(const HopArgs& a, const Issue& is) {
+    constexpr int S = HOP_NP / 4;
+    if constexpr (HOP_NP == 4) {
+        if (a.r12) {
+            if constexpr (EPI != EPI_XPAY)
+                if (a.lazy_r) return run_hop1<P, S, EPI, true, true>(a, is);
+            return run_hop1<P, S, EPI, true, false>(a, is);
+        }
+    }
+    if constexpr (EPI != EPI_XPAY)
+        if (a.lazy_r) return run_hop1<P, S, EPI, false, true>(a, is);
+    return run_hop1<P, S, EPI, false, false>(a, is);
+}
+
 template <int P, int S, int N, int EPI, bool NT>
 static hipError_t run_hop(const HopArgs& a, const Issue& is) {
     HopArgs arg = a;
@@ -420,6 +656,11 @@ static hipError_t run_block(int S, const HopArgs& a, const Issue& is) {
 template <int P, int EPI>
 static hipError_t dispatch_epi(int S, int N, bool nt, const HopArgs& a, const Issue& is) {
     if (N == 1) {
+        if constexpr (EPI != EPI_RESID && kUseHop1<P, HOP_NP>) {
+            if (nt && S == HOP_NP / 4 && !a.lazy_y && !a.gate && a.g.Vh < kHop1MaxSites &&
+                !(EPI == EPI_XPAY && a.lazy_r) && !(a.fin.partials && (EPI != EPI_PLAIN || !a.lazy_r)))
+                return dispatch_hop1<P, EPI>(a, is);
+        }
         if (nt) {
             if (S == 1) return run_hop<P, 1, 1, EPI, true>(a, is);
             if (S == 2) return run_hop<P, 2, 1, EPI, true>(a, is);

@@ -194,33 +194,53 @@ struct PairRaw<P16S> {
     float sc;
 };
 
-template <int P, bool NT>
-__device__ __forceinline__ void load_pair_raw(const void* G, const float* gscale, uint32_t Vh,
-                                              uint32_t s, int mu, int r12, PairRaw<P>& w) {
+// Start of hop pair mu of site s in the tiled links (common.h), without the
+// site's own offset in a plane. A wavefront's sites lie in one tile whatever
+// the launch shape (1, 2 or 4 lanes per site, aligned runs of at most 64
+// sites), so the tile's address is kept in scalar registers and a plane is an
+// offset to it: no 64-bit address per word in the vector registers.
+template <int P, int NP>
+__device__ __forceinline__ const char* pair_tile(const void* G, uint32_t s, int mu, int r12) {
+    const uint32_t pb = link_pair_bytes(P, r12);
+    const uint32_t tile = __builtin_amdgcn_readfirstlane(s / kLinkTile);
+    return (const char*)G + (size_t)tile * (kLinkTile * NP * pb) + (uint32_t)mu * (kLinkTile * pb);
+}
+
+template <int P, bool NT, int NP>
+__device__ __forceinline__ void load_pair_raw(const void* G, const float* gscale, uint32_t s,
+                                              int mu, int r12, PairRaw<P>& w) {
+    const char* tile = pair_tile<P, NP>(G, s, mu, r12);
+    const uint32_t i = s % kLinkTile;
     if constexpr (P == P64) {
-        const d2v* g = (const d2v*)G + (size_t)((r12 ? 12 : 18) * mu) * Vh + s;
+        const d2v* g = (const d2v*)tile;
 #pragma unroll
-        for (int e = 0; e < 12; ++e) w.v[e] = ldg<NT>(g + (size_t)e * Vh);
+        for (int e = 0; e < 12; ++e) w.v[e] = ldg<NT>(g + (e * kLinkTile + i));
         if (!r12) {
 #pragma unroll
-            for (int e = 12; e < 18; ++e) w.v[e] = ldg<NT>(g + (size_t)e * Vh);
+            for (int e = 12; e < 18; ++e) w.v[e] = ldg<NT>(g + (e * kLinkTile + i));
         }
     } else if constexpr (P == P32) {
-        const f4v* g = (const f4v*)G + (size_t)((r12 ? 6 : 9) * mu) * Vh + s;
+        const f4v* g = (const f4v*)tile;
 #pragma unroll
-        for (int e = 0; e < 6; ++e) w.v[e] = ldg<NT>(g + (size_t)e * Vh);
+        for (int e = 0; e < 6; ++e) w.v[e] = ldg<NT>(g + (e * kLinkTile + i));
         if (!r12) {
 #pragma unroll
-            for (int e = 6; e < 9; ++e) w.v[e] = ldg<NT>(g + (size_t)e * Vh);
+            for (int e = 6; e < 9; ++e) w.v[e] = ldg<NT>(g + (e * kLinkTile + i));
         }
     } else {
-        const u2v* g = (const u2v*)G + (size_t)((r12 ? 6 : 9) * mu) * Vh + s;
+        const u4v* g = (const u4v*)tile;
         w.sc = gscale[s];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) w.v[e] = ldg<NT>(g + (size_t)e * Vh);
+        for (int e = 0; e < 3; ++e) {
+            const u4v q = ldg<NT>(g + (e * kLinkTile + i));
+            w.v[2 * e] = q.xy;
+            w.v[2 * e + 1] = q.zw;
+        }
         if (!r12) {
-#pragma unroll
-            for (int e = 6; e < 9; ++e) w.v[e] = ldg<NT>(g + (size_t)e * Vh);
+            const u4v q = ldg<NT>(g + (3 * kLinkTile + i));
+            w.v[6] = q.xy;
+            w.v[7] = q.zw;
+            w.v[8] = ldg<NT>((const u2v*)(g + 4 * kLinkTile) + i);
         }
     }
 }
@@ -311,14 +331,13 @@ __device__ __forceinline__ void finish_pair(int r12, int eta, const PairRaw<P>& 
 }
 
 // Both steps at once: hop pair mu of output site s, ready to apply.
-template <int P, bool NT>
-__device__ __forceinline__ void load_pair(const void* G, const float* gscale, uint32_t Vh,
-                                          uint32_t s, int mu, int r12, int eta,
-                                          typename Real<P>::T (&lr)[18],
+template <int P, bool NT, int NP>
+__device__ __forceinline__ void load_pair(const void* G, const float* gscale, uint32_t s, int mu,
+                                          int r12, int eta, typename Real<P>::T (&lr)[18],
                                           typename Real<P>::T (&li)[18],
                                           PairScale<typename Real<P>::T>& ps) {
     PairRaw<P> w;
-    load_pair_raw<P, NT>(G, gscale, Vh, s, mu, r12, w);
+    load_pair_raw<P, NT, NP>(G, gscale, s, mu, r12, w);
     finish_pair<P>(r12, eta, w, lr, li, ps);
 }
 

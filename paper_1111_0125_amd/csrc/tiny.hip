@@ -56,7 +56,7 @@ __device__ __forceinline__ void tiny_hop(const void* G, const float* gscale, con
         neighbours(g, s, x, y, z, t, j, nf, nb);
         T lr[18], li[18];
         PairScale<T> ps;
-        load_pair<P, false>(G, gscale, g.Vh, s, j, r12, eta_sign(j, x, y, z), lr, li, ps);
+        load_pair<P, false, 4>(G, gscale, s, j, r12, eta_sign(j, x, y, z), lr, li, ps);
         T vr[3], vi[3];
         load_site<P>(in, g.Vh, nf, vr, vi);
         pair_start(lr, li, vr, vi, ar, ai);
