@@ -39,6 +39,7 @@ UNITS = [
     ("blas.hip", "blas.o", []),
     ("layout.hip", "layout.o", []),
     ("tiny.hip", "tiny.o", []),
+    ("persist.hip", "persist.o", []),
     ("scratch.hip", "scratch.o", []),
     ("capi.cpp", "capi.o", []),
     ("solver.cpp", "solver.o", []),

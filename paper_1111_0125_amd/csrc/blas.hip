@@ -40,29 +40,35 @@ __device__ __forceinline__ void load_upd(const VecArgs& a, int r, uint32_t s, Up
     load_site<P>(slot(a, 3, r), a.Vh, s, u.qr, u.qi);
 }
 
-template <int P, int N, int OP>
+// T256 consecutive runs of 256 sites per block, one site per thread at a time:
+// a block that finalises a reduction sums the partials of the whole lattice
+// first, and several runs share that (vec_runs).
+template <int P, int N, int OP, int T256>
 __global__ __launch_bounds__(kBlock) void k_vec(VecArgs a) {
     using T = typename Real<P>::T;
-    const uint32_t blk = logical_block(a.swizzle);
-    const uint32_t s = blk * kBlock + threadIdx.x;
+    const uint32_t run0 = logical_block(a.swizzle) * T256;
+    const uint32_t s0 = run0 * kBlock + threadIdx.x;
     const uint32_t Vh = a.Vh;
-    const bool valid = s < Vh;
     // Per-RHS state, finalised here from the previous reduction's partials
-    // when a.fin is set. One RHS: each wavefront keeps it in registers (no
-    // barrier) and an update requests its operands and the partials before
-    // the state is known (an inactive slot discards them). Several RHS: the
-    // block shares one copy in LDS.
+    // when a.fin is set. One RHS and one run per block: each wavefront keeps it
+    // in registers (no barrier). Else the block shares one copy in LDS, with
+    // several runs summed by all wavefronts together. With one RHS an update
+    // requests its first operands before the state is known (an inactive slot
+    // discards them).
     constexpr bool UPD = OP == OP_UPD_CG || OP == OP_UPD_MIXED;
+    constexpr bool REG = N == 1 && T256 == 1;
     __shared__ RhsState ls[N];
     RhsState s1{};
     unsigned act = (1u << N) - 1u;
     [[maybe_unused]] UpdOps<P, OP> u0;
-    if constexpr (N == 1) {
+    if constexpr (REG) {
         s1 = *(a.st ? a.st : &kNoState);
         if (a.st && !(s1.flags & a.run_mask)) act = 0;
-        if constexpr (UPD) {
-            if (valid) load_upd<P, OP>(a, 0, s, u0);
-        }
+    }
+    if constexpr (N == 1 && UPD) {
+        if (s0 < Vh) load_upd<P, OP>(a, 0, s0, u0);
+    }
+    if constexpr (REG) {
         if (a.st && a.fin.partials) {
             // always: block 0 must pass the state on even when it is inactive
             Reduce F = a.fin;
@@ -74,7 +80,11 @@ __global__ __launch_bounds__(kBlock) void k_vec(VecArgs a) {
         if (a.fin.partials) {
             Reduce F = a.fin;
             F.st = a.st;
-            finalize_block<N>(F, a.run_mask, ls);
+            if constexpr (T256 == 1) {
+                finalize_block<N>(F, a.run_mask, ls);
+            } else {
+                finalize_coop<N>(F, a.run_mask, ls);
+            }
         } else {
             load_state<N>(a.st, ls);
         }
@@ -84,12 +94,16 @@ __global__ __launch_bounds__(kBlock) void k_vec(VecArgs a) {
             if (ls[r].flags & a.run_mask) act |= 1u << r;
     }
     auto stv = [&](int r) -> const RhsState& {
-        if constexpr (N == 1) {
+        if constexpr (REG) {
             return s1;
         } else {
             return ls[r];
         }
     };
+#pragma unroll 1
+    for (int k = 0; k < T256; ++k) {
+    const uint32_t s = s0 + k * kBlock;
+    const bool valid = s < Vh;
     double dv[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) dv[r] = 0.0;
@@ -128,7 +142,7 @@ __global__ __launch_bounds__(kBlock) void k_vec(VecArgs a) {
                 // x += alpha d; r -= alpha Ad; |r|^2   (all fp64)
                 const double al = stv(r).alpha;
                 UpdOps<P, OP> u;
-                if constexpr (N == 1) {
+                if (N == 1 && k == 0) {
                     u = u0;
                 } else {
                     load_upd<P, OP>(a, r, s, u);
@@ -149,7 +163,7 @@ __global__ __launch_bounds__(kBlock) void k_vec(VecArgs a) {
                 // y += alpha d (fp32); rs = q(rs - alpha Ad); |rs|^2 of the stored rs
                 const float al = (float)stv(r).alpha;
                 UpdOps<P, OP> u;
-                if constexpr (N == 1) {
+                if (N == 1 && k == 0) {
                     u = u0;
                 } else {
                     load_upd<P, OP>(a, r, s, u);
@@ -198,16 +212,31 @@ __global__ __launch_bounds__(kBlock) void k_vec(VecArgs a) {
         }
     }
     if constexpr (OP == OP_INIT_B || OP == OP_UPD_CG || OP == OP_UPD_MIXED) {
-        block_partials<N>(dv, a.red, blk);
+        if (k > 0) __syncthreads();  // the run before may still be read from LDS
+        block_partials<N, 1>(dv, a.red, run0 + k);
+    }
     }
 }
+
+// Runs of 256 sites per block: two where that leaves two blocks per compute
+// unit, for the kernels that finalise a reduction (24^3 x 48 fp32, 1296 partials:
+// update 9.8 us against 11.6 with one run and every wavefront summing for
+// itself and 7.6 when a one-block kernel of 4.9 us does; direction pass 6.8, 8.2
+// and 5.5).
+static int vec_runs(const VecArgs& a) { return a.fin.partials && vec_blocks(a.Vh) >= 2 * 512 ? 2 : 1; }
 
 template <int P, int N, int OP>
 static hipError_t issue_vec(const VecArgs& a, const Issue& is) {
     VecArgs arg = a;
     void* args[] = {&arg};
-    return issue_kernel(is, reinterpret_cast<const void*>(&k_vec<P, N, OP>), vec_blocks(a.Vh), kBlock,
-                        args);
+    const int t = vec_runs(a);
+    const void* f = reinterpret_cast<const void*>(&k_vec<P, N, OP, 1>);
+    if constexpr (OP == OP_UPD_CG || OP == OP_UPD_MIXED || OP == OP_XPAY) {
+        if (t == 2) f = reinterpret_cast<const void*>(&k_vec<P, N, OP, 2>);
+    } else if (t > 1) {
+        return hipErrorInvalidValue;
+    }
+    return issue_kernel(is, f, (vec_blocks(a.Vh) + t - 1) / t, kBlock, args);
 }
 
 template <int P, int N>

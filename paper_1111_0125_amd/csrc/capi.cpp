@@ -244,6 +244,10 @@ int stag_create(int device, size_t hbm_budget_bytes, stag_ctx** out) {
     stag_ctx* c = new stag_ctx();
     c->device = device;
     c->stream = s;
+    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+        (void)hipGetLastError();
+        c->cus = 0;  // no resident kernels
+    }
     c->scratch = scr;
     c->pool = pool;
     if (hbm_budget_bytes == 0) {

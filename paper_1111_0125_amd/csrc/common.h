@@ -258,19 +258,21 @@ enum FinKind : int {
     FIN_TRUE = 12,     // rr_true = sum
 };
 
-// A reduction: the producing kernel writes one fp64 partial per 64-site
-// chunk and right-hand side; its consumer sums them in a fixed order and
+// A reduction: each block of the producing kernel writes one fp64 partial per
+// right-hand side (sub of them make up 256 consecutive sites); its consumer
+// sums them in a fixed order and
 // applies `kind` to the state. The consumer reads the state from st and
 // writes the result to st_out (st_out null: in place, one-block consumers
 // only), so a many-block consumer never reads what one of its own blocks
 // has already overwritten.
 struct Reduce {
-    double* partials;   // [nrhs][nparts]: one partial per 64-site chunk
+    double* partials;   // [nrhs][nparts]: one partial per block of the producer
     RhsState* st;       // [nrhs] state read
     double* out;        // FIN_STORE destination [nrhs]
     RhsState* st_out;   // [nrhs] state written (null: st)
     int kind;
     int nparts;
+    int sub;            // partials per 256 sites (the producer's lanes per site: 1, 2 or 4)
 };
 
 }  // namespace stag

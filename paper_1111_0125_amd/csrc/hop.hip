@@ -396,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_hop(HopArgs a) {
         }
     }
     if constexpr (EPI == EPI_XPAY_DOT || EPI == EPI_RESID) {
-        block_chunk_partials<N, S>(dv, a.red, blk);
+        block_partials<N, S>(dv, a.red, blk);
     }
 }
 
@@ -594,7 +594,7 @@ __global__ __launch_bounds__(kBlock) void k_hop1(HopArgs a) {
             }
         }
     }
-    if constexpr (EPI == EPI_XPAY_DOT) block_chunk_partials<1, S>(dv, a.red, blk);
+    if constexpr (EPI == EPI_XPAY_DOT) block_partials<1, S>(dv, a.red, blk);
 }
 
 // k_hop1 serves the default launch shape (non-temporal link loads, four pairs

@@ -58,6 +58,7 @@ struct Timing {
 struct stag_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
+    int cus = 0;                   // compute units
     void* scratch = nullptr;       // this device's copy of the scratch array (scratch.hip)
     hipMemPool_t pool = nullptr;   // stream-ordered temporaries; keeps freed memory for reuse
     size_t budget = 0;
@@ -126,6 +127,11 @@ struct stag_engine {
     // so a consumer reads one while writing the other.
     double* partials = nullptr;
     double* partials1 = nullptr;
+    // Exchange buffer of the resident kernel (small lattices): tagged partials
+    // per slot; the abort word follows the states, so a poll brings it along.
+    // tag: the next unused one.
+    unsigned long long* ex = nullptr;
+    uint32_t tag = 0;
     size_t bytes = 0;
     std::map<long long, hipGraphExec_t> graphs;    // one block of work; key: (K, kernel N)
     stag::HopTune tune_lo, tune_64;
@@ -144,6 +150,8 @@ struct EngineRun {
     int variant = 0;          // mixed CG variant (MixedVariant), the same for every slot
     bool use_graph = true;
     bool timed = false;
+    int persist = 0;          // > 0: resident-kernel iterations with this many lanes per site
+    int nrhs = 0;             // right-hand sides of a resident-kernel run
     long long launched = 0;   // blocks enqueued (block j polls into buffer j % 2)
     long long polled = 0;     // polls processed
     long long last_poll = -1; // index of the last processed poll

@@ -641,36 +641,90 @@ __device__ __forceinline__ void finalize_one(int kind, RhsState* sp, double sum,
     }
 }
 
-// Reduction partials are taken over fixed chunks of 64 consecutive sites,
-// whatever the launch shape, and each chunk is summed by the same butterfly
-// over the site index (the vector kernels, which have one launch shape, add
-// a block's four chunk sums into one partial: block_partials); the consumer
-// of a reduction then sums the partials of each right-hand side with one
-// wavefront in a fixed order (wave_sum_partials). The result is therefore independent of how many
-// lanes serve a site, of how many right-hand sides share the kernel and of
-// which kernel forms the sum. No block waits for another and no atomics are
-// used: on this chip cross-block atomics serialise (tens of ns per block),
-// which made an in-kernel "last block finalises" tail cost several
-// microseconds.
+// The lane exchanges of a wavefront butterfly, for two 32-bit halves of a
+// double, without LDS traffic (a __shfl_xor is a round trip through LDS, about
+// 60 ns each way; six of them were a third of a reduction's latency in the
+// resident kernel). DPP: quad permutes for 1 and 2, half-row mirror
+// (lane ^ 7) after a quad reversal (lane ^ 3) for 4, row rotation for 8.
+template <int OFF>
+__device__ __forceinline__ unsigned lane_xor_dpp(unsigned v) {
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "within a row of 16 lanes");
+    if constexpr (OFF == 1) return __builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xf, 0xf, true);
+    if constexpr (OFF == 2) return __builtin_amdgcn_update_dpp(0u, v, 0x4E, 0xf, 0xf, true);
+    if constexpr (OFF == 4)
+        return __builtin_amdgcn_update_dpp(
+            0u, __builtin_amdgcn_update_dpp(0u, v, 0x1B, 0xf, 0xf, true), 0x141, 0xf, 0xf, true);
+    return __builtin_amdgcn_update_dpp(0u, v, 0x128, 0xf, 0xf, true);
+}
+
+// x + (x of lane ^ OFF); every lane of the wavefront calls it.
+template <int OFF>
+__device__ __forceinline__ double add_lane_xor(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+    if constexpr (OFF >= 16) {
+        // the swap of two copies leaves the lower row (half) in one result and
+        // the upper in the other on every lane: their sum is the butterfly's
+        // (addition commutes)
+        unsigned l0, l1, h0, h1;
+        if constexpr (OFF == 32) {
+            auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+        } else {
+            auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+        }
+        return __longlong_as_double((long long)(((unsigned long long)h0 << 32) | l0)) +
+               __longlong_as_double((long long)(((unsigned long long)h1 << 32) | l1));
+    } else {
+        const unsigned l = lane_xor_dpp<OFF>(lo), h = lane_xor_dpp<OFF>(hi);
+        return x + __longlong_as_double((long long)(((unsigned long long)h << 32) | l));
+    }
+}
+
+// Butterfly sum over the wavefront (lane ^ 32, 16, ..., 1), on every lane.
+__device__ __forceinline__ double wave_butterfly(double x) {
+    x = add_lane_xor<32>(x);
+    x = add_lane_xor<16>(x);
+    x = add_lane_xor<8>(x);
+    x = add_lane_xor<4>(x);
+    x = add_lane_xor<2>(x);
+    return add_lane_xor<1>(x);
+}
+
+// Reductions are taken over fixed chunks of 64 consecutive sites, whatever the
+// launch shape, each summed by the same butterfly over the site index, and
+// four consecutive chunks (256 sites) are added as (c0 + c1) + (c2 + c3). A
+// block writes one partial: with one lane per site those four chunks, with
+// two lanes c0 + c1 or c2 + c3, with four a single chunk; the consumer
+// completes the groups (Reduce::sub partials each) and sums the groups of each
+// right-hand side with one wavefront in a fixed order (wave_sum_partials). The
+// result is therefore independent of how many lanes serve a site, of how many
+// right-hand sides share the kernel and of which kernel forms the sum. No
+// block waits for another and no atomics are used: on this chip cross-block
+// atomics serialise (tens of ns per block), which made an in-kernel "last
+// block finalises" tail cost several microseconds.
 constexpr int kChunk = 64;
+static_assert(kBlock == 4 * kChunk, "a block's threads are four chunks of lanes");
 
 // v[r] is the value of the site handled by this thread (meaningful on the
 // first lane of each site, i.e. threadIdx.x % S == 0); the block covers
 // kBlock / S consecutive sites starting at blk * (kBlock / S).
 template <int N, int S>
-__device__ __forceinline__ void block_chunk_partials(double (&v)[N], const Reduce& R, uint32_t blk) {
+__device__ __forceinline__ void block_partials(double (&v)[N], const Reduce& R, uint32_t blk) {
     constexpr int SPB = kBlock / S;          // sites per block
-    constexpr int CPB = SPB / kChunk;        // chunks per block (>= 1)
+    constexpr int CPB = SPB / kChunk;        // chunks per block: 4, 2 or 1
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ double sw[N][CPB];
     if constexpr (S == 1) {
         // one wave is one chunk: reduce straight from registers
 #pragma unroll
         for (int r = 0; r < N; ++r) {
             double x = v[r];
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-            const uint32_t ch = blk * CPB + wave;
-            if (lane == 0 && ch < (uint32_t)R.nparts) R.partials[(size_t)r * R.nparts + ch] = x;
+            x = wave_butterfly(x);
+            if (lane == 0) sw[r][wave] = x;
         }
     } else {
         __shared__ double sv[N][SPB];
@@ -683,41 +737,32 @@ __device__ __forceinline__ void block_chunk_partials(double (&v)[N], const Reduc
 #pragma unroll
             for (int r = 0; r < N; ++r) {
                 double x = sv[r][wave * kChunk + lane];
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-                const uint32_t ch = blk * CPB + wave;
-                if (lane == 0 && ch < (uint32_t)R.nparts) R.partials[(size_t)r * R.nparts + ch] = x;
+                x = wave_butterfly(x);
+                if (lane == 0) sw[r][wave] = x;
             }
         }
-    }
-}
-
-// One thread per site, kBlock sites per block (the vector kernels): the
-// partial of each right-hand side is the block's, its four 64-site chunk
-// sums (the butterfly of block_chunk_partials) added as (c0 + c1) + (c2 + c3).
-// A quarter of the chunk count to sum for the reduction's consumers, and
-// still the same whatever the launch (the vector kernels have one shape).
-template <int N>
-__device__ __forceinline__ void block_partials(double (&v)[N], const Reduce& R, uint32_t blk) {
-    static_assert(kBlock == 4 * kChunk, "a block is four chunks");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __shared__ double sw[N][4];
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-        double x = v[r];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-        if (lane == 0) sw[r][wave] = x;
     }
     __syncthreads();
     if (threadIdx.x < N && blk < (uint32_t)R.nparts) {
         const int r = threadIdx.x;
-        R.partials[(size_t)r * R.nparts + blk] = (sw[r][0] + sw[r][1]) + (sw[r][2] + sw[r][3]);
+        double x = sw[r][0];
+        if constexpr (CPB == 2) x = sw[r][0] + sw[r][1];
+        if constexpr (CPB == 4) x = (sw[r][0] + sw[r][1]) + (sw[r][2] + sw[r][3]);
+        R.partials[(size_t)r * R.nparts + blk] = x;
     }
 }
 
-// Fixed-order sum of one right-hand side's chunk partials by one
-// wavefront: lane l accumulates partials l, l + 64, l + 128, ... into four
+// Group g of a reduction's partials: 256 sites, written as sub partials by the
+// producer (a partial past the end is an empty chunk, 0).
+__device__ __forceinline__ double group_partial(const double* pp, int nparts, int sub, int g) {
+    if (sub == 1) return pp[g];
+    auto at = [&](int i) { return i < nparts ? pp[i] : 0.0; };
+    if (sub == 2) return at(2 * g) + at(2 * g + 1);
+    return (at(4 * g) + at(4 * g + 1)) + (at(4 * g + 2) + at(4 * g + 3));
+}
+
+// Fixed-order sum of one right-hand side's groups of partials by one
+// wavefront: lane l accumulates groups l, l + 64, l + 128, ... into four
 // interleaved running sums, combined as (s0 + s1) + (s2 + s3) and then
 // across the wave by a butterfly. Every lane returns the same value (each
 // exchange adds the same two numbers on both partners). U only sets how
@@ -725,10 +770,26 @@ __device__ __forceinline__ void block_partials(double (&v)[N], const Reduce& R, 
 // sum is bound by memory latency when the partials are many); the order of
 // the additions, and so the result, is the same for every U.
 template <int U = 4>
-__device__ __forceinline__ double wave_sum_partials(const double* pp, int nparts) {
+__device__ __forceinline__ double wave_sum_partials(const double* pp, int nparts, int sub) {
     const int lane = threadIdx.x & 63;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int i = lane;
+    if (sub > 1) {
+        // launch shapes of several lanes per site
+        const int groups = (nparts + sub - 1) / sub;
+        for (; i + 192 < groups; i += 256) {
+            s0 += group_partial(pp, nparts, sub, i);
+            s1 += group_partial(pp, nparts, sub, i + 64);
+            s2 += group_partial(pp, nparts, sub, i + 128);
+            s3 += group_partial(pp, nparts, sub, i + 192);
+        }
+        if (i < groups) s0 += group_partial(pp, nparts, sub, i);
+        if (i + 64 < groups) s1 += group_partial(pp, nparts, sub, i + 64);
+        if (i + 128 < groups) s2 += group_partial(pp, nparts, sub, i + 128);
+        double x = (s0 + s1) + (s2 + s3);
+        x = wave_butterfly(x);
+        return x;
+    }
     if constexpr (U > 4) {
         for (; i + (256 * U - 64) < nparts; i += 256 * U) {
             double v[4 * U];
@@ -754,8 +815,7 @@ __device__ __forceinline__ double wave_sum_partials(const double* pp, int nparts
     if (i + 64 < nparts) s1 += pp[i + 64];
     if (i + 128 < nparts) s2 += pp[i + 128];
     double x = (s0 + s1) + (s2 + s3);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+    x = wave_butterfly(x);
     return x;
 }
 
@@ -779,7 +839,7 @@ template <int N>
 __device__ __forceinline__ void finalize_wide(const Reduce& R, unsigned run_mask, RhsState* ls) {
     constexpr int U = N <= 8 ? 16 : 8;  // loads in flight within the register budget
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const double sum = wave_sum_partials<U>(R.partials + (size_t)wave * R.nparts, R.nparts);
+    const double sum = wave_sum_partials<U>(R.partials + (size_t)wave * R.nparts, R.nparts, R.sub);
     if (!R.st) {
         if (lane == 0 && R.out) R.out[wave] = sum;
         return;
@@ -806,7 +866,7 @@ __device__ __forceinline__ void finalize_block(const Reduce& R, unsigned run_mas
     const int nw = blockDim.x >> 6;
     if (!R.st) {
         for (int r = wave; r < N; r += nw) {
-            const double sum = wave_sum_partials(R.partials + (size_t)r * R.nparts, R.nparts);
+            const double sum = wave_sum_partials(R.partials + (size_t)r * R.nparts, R.nparts, R.sub);
             if (lane == 0 && blockIdx.x == 0 && R.out) R.out[r] = sum;
         }
         return;
@@ -814,8 +874,50 @@ __device__ __forceinline__ void finalize_block(const Reduce& R, unsigned run_mas
     load_state<N>(R.st, ls);
     for (int r = wave; r < N; r += nw) {
         if (!(ls[r].flags & run_mask)) continue;  // uniform over the wave
-        const double sum = wave_sum_partials(R.partials + (size_t)r * R.nparts, R.nparts);
+        const double sum = wave_sum_partials(R.partials + (size_t)r * R.nparts, R.nparts, R.sub);
         if (lane == 0) finalize_one(R.kind, ls + r, sum, blockIdx.x == 0 && R.out ? R.out + r : nullptr);
+    }
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        unsigned long long* dst = (unsigned long long*)(R.st_out ? R.st_out : R.st);
+        const unsigned long long* src = (const unsigned long long*)ls;
+        for (int i = threadIdx.x; i < N * kStateWords; i += blockDim.x) dst[i] = src[i];
+    }
+}
+
+// finalize_block for a vector kernel (kBlock threads), whose every block sums
+// the partials of a whole lattice: the four running sums of wave_sum_partials
+// are taken by the block's four wavefronts, each with several loads in flight,
+// so a block's latency is a quarter of the single wavefront's. Same additions
+// in the same order.
+template <int N>
+__device__ __forceinline__ void finalize_coop(const Reduce& R, unsigned run_mask, RhsState* ls) {
+    static_assert(kBlock == 256, "four wavefronts");
+    constexpr int U = 8;
+    __shared__ double sp[N][4][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int groups = (R.nparts + R.sub - 1) / R.sub;
+#pragma unroll 1
+    for (int r = 0; r < N; ++r) {
+        const double* pp = R.partials + (size_t)r * R.nparts;
+        double s = 0.0;
+        for (int i = (int)threadIdx.x; i < groups; i += 256 * U) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                v[u] = i + 256 * u < groups ? group_partial(pp, R.nparts, R.sub, i + 256 * u) : 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + 256 * u < groups) s += v[u];
+        }
+        sp[r][wave][lane] = s;
+    }
+    load_state<N>(R.st, ls);  // ends with a barrier
+    for (int r = wave; r < N; r += 4) {
+        double x = (sp[r][0][lane] + sp[r][1][lane]) + (sp[r][2][lane] + sp[r][3][lane]);
+        x = wave_butterfly(x);
+        if (lane == 0 && (ls[r].flags & run_mask))
+            finalize_one(R.kind, ls + r, x, blockIdx.x == 0 && R.out ? R.out + r : nullptr);
     }
     __syncthreads();
     if (blockIdx.x == 0) {
@@ -849,7 +951,7 @@ static __device__ RhsState kNoState{};
 __device__ __forceinline__ void finalize_wave1(const Reduce& R, unsigned run_mask, RhsState& s) {
     // summed before the flags are read: the partials' loads then need not
     // wait for the state's
-    const double sum = wave_sum_partials(R.partials, R.nparts);
+    const double sum = wave_sum_partials(R.partials, R.nparts, R.sub);
     if (s.flags & run_mask) {
         const bool t0 = blockIdx.x == 0 && threadIdx.x == 0;
         finalize_one(R.kind, &s, sum, t0 && R.out ? R.out : nullptr);

@@ -167,7 +167,34 @@ struct TinyArgs {
 
 hipError_t launch_tiny(int prec, int nrhs, const TinyArgs& a, hipStream_t stream);
 
-// Reduction partials: one per 64-site chunk, whatever the launch shape.
+// Iterations of small lattices in one resident kernel (persist.hip): a group
+// of `blocks` workgroups per right-hand side, S lanes per site.
+constexpr int kPersistBlocks = 256;  // most blocks per right-hand side
+
+struct PersistArgs {
+    const void* G[2];        // inner-precision hop links by output parity
+    const float* gscale[2];  // P16S site scales
+    Geom g;
+    // slot-strided buffers: direction, D_oe d, iterated residual (plain CG:
+    // the fp64 buffers) and the fp32 correction (plain CG: x64)
+    void* d;
+    void* t;                    // two buffers for D_oe d (the second: A d's,
+    void* t2;                   // which stays in registers)
+    void* r;
+    void* y;
+    size_t rsP, rsY;
+    RhsState* st;               // [nrhs]
+    unsigned long long* ex;     // [nrhs][2][kPersistBlocks][2] tagged partials
+    int* abort;                 // set when a wait ran out
+    int nrhs, blocks, one_xcd;
+    int max_iters;              // iterations per launch
+    uint32_t tag;               // even; tag + 1 .. tag + 2 max_iters + 1 are used and were not before
+    long long limit;            // longest wait, ticks of 10 ns
+};
+
+hipError_t launch_persist(int prec, int S, bool r12, const PersistArgs& a, hipStream_t stream);
+
+// Most partials of a reduction: four lanes per site, one per 64 sites.
 inline uint32_t num_chunks(uint32_t Vh) { return (Vh + 63) / 64; }
 
 inline uint32_t hop_blocks(uint32_t Vh, int S) {

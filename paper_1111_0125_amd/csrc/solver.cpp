@@ -26,6 +26,13 @@
 namespace stag {
 
 static size_t state_bytes(int N) { return sizeof(RhsState) * (size_t)N; }
+constexpr size_t kAbortBytes = 8;  // the resident kernel's abort word, behind the states
+
+// Whether a resident kernel can serve an engine's lattice at all.
+static bool persist_capable(const stag_gauge* g) {
+    return g->npairs == 4 && g->g.Vh <= (uint32_t)kPersistBlocks * kBlock;
+}
+static size_t ex_bytes(int N) { return (size_t)N * 4 * kPersistBlocks * sizeof(unsigned long long); }
 
 void engine_drop_graphs(stag_engine* e) {
     for (auto& kv : e->graphs)
@@ -38,7 +45,7 @@ void engine_destroy(stag_engine* e) {
     stag_ctx* ctx = e->ctx;
     engine_drop_graphs(e);
     void* bufs[] = {e->x64, e->r64, e->t64, e->d64, e->Ad64, e->y32, e->rs, e->d, e->t, e->Ad,
-                    e->b64, e->st, e->st1, e->partials, e->partials1};
+                    e->b64, e->st, e->st1, e->partials, e->partials1, e->ex};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     for (int i = 0; i < 2; ++i) {
@@ -69,7 +76,7 @@ int engine_create(stag_ctx* ctx, const stag_gauge* g, int prec, int N, bool serv
     };
     std::vector<Req> reqs = {
         {&e->x64, N * e->rs64}, {&e->r64, N * e->rs64}, {&e->t64, N * e->rs64},
-        {(void**)&e->st, state_bytes(N)}, {(void**)&e->st1, state_bytes(N)},
+        {(void**)&e->st, state_bytes(N) + kAbortBytes}, {(void**)&e->st1, state_bytes(N)},
         {(void**)&e->partials, N * nparts * sizeof(double)},
         {(void**)&e->partials1, N * nparts * sizeof(double)},
     };
@@ -77,6 +84,7 @@ int engine_create(stag_ctx* ctx, const stag_gauge* g, int prec, int N, bool serv
     // the iteration graphs read them, so their address must not change
     reqs.push_back({&e->b64, N * e->rs64});
     e->serving = serving;
+    if (!serving && persist_capable(g)) reqs.push_back({(void**)&e->ex, ex_bytes(N)});
     if (prec == P64) {
         reqs.push_back({&e->d64, N * e->rs64});
         reqs.push_back({&e->Ad64, N * e->rs64});
@@ -105,7 +113,7 @@ int engine_create(stag_ctx* ctx, const stag_gauge* g, int prec, int N, bool serv
         }
     }
     for (int i = 0; i < 2; ++i) {
-        if (hipHostMalloc((void**)&e->host[i], state_bytes(N), hipHostMallocDefault) != hipSuccess ||
+        if (hipHostMalloc((void**)&e->host[i], state_bytes(N) + kAbortBytes, hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&e->ev[i], hipEventDisableTiming) != hipSuccess) {
             (void)hipGetLastError();
             engine_destroy(e);
@@ -122,7 +130,7 @@ int engine_create(stag_ctx* ctx, const stag_gauge* g, int prec, int N, bool serv
     // is then waited for (only it: other streams' work is not held up), so
     // whatever stream the engine is used on later sees the cleared buffers.
     hipStream_t s = init_stream;
-    hipError_t err = hipMemsetAsync(e->st, 0, state_bytes(N), s);
+    hipError_t err = hipMemsetAsync(e->st, 0, state_bytes(N) + kAbortBytes, s);
     if (err == hipSuccess) err = hipMemsetAsync(e->st1, 0, state_bytes(N), s);
     if (err == hipSuccess && e->d64) err = hipMemsetAsync(e->d64, 0, N * e->rs64, s);
     if (err == hipSuccess && e->d) err = hipMemsetAsync(e->d, 0, N * e->rsP, s);
@@ -166,13 +174,15 @@ void engine_release(stag_engine* e) {
 
 // ------------------------------------------------------------------ enqueue helpers
 
-// Finalising a reduction at the start of its consumer costs every wave (one
-// RHS) or every block (several) one pass over all the chunk partials of the
-// RHS it serves. That pays on small lattices, where a separate one-block
-// kernel and its launch would be a large part of an iteration, and not on
-// large ones, where the passes would add up to a sizeable fraction of the
-// kernel's own traffic. Above this many partials per consumer the reduction
-// is finalised by a one-block kernel and consumers read the state.
+// Finalising a reduction at the start of its consumer costs every block one
+// pass over the partials of the right-hand sides it serves. That pays on
+// lattices where a separate one-block kernel and its launch are a large part of
+// an iteration, and not where the passes add up to a sizeable fraction of the
+// kernel's own traffic; above this many partials per consumer the reduction
+// is finalised by a one-block kernel and consumers read the state. Measured,
+// per solve: 24^3 x 48 fp32 (1296 partials) 135.5 ms against 141.4 with the
+// one-block kernel, with 4 RHS (5184) 230.5 against 228.2; 32^3 x 64 fp16 (4096)
+// 111.6 against 108.0.
 constexpr size_t kFuseMaxPartials = 2048;
 
 // Kernels of any number of right-hand sides run the direction update as
@@ -184,7 +194,7 @@ constexpr uint32_t kXpayMinSites = 131072;
 constexpr int kXpayMinRhs = 8;
 
 bool fuse_finalize(const stag_engine* e, int nk) {
-    return (size_t)num_chunks(e->Vh) * (size_t)nk <= kFuseMaxPartials;
+    return (size_t)vec_blocks(e->Vh) * (size_t)nk <= kFuseMaxPartials;
 }
 
 namespace {
@@ -215,22 +225,16 @@ hipError_t timed_launch(const Ctx& c, int kind, F&& fn) {
     return hipSuccess;
 }
 
-Reduce make_red(stag_engine* e, int kind, double* partials = nullptr) {
+// A reduction produced with S lanes per site (the vector kernels: 1).
+Reduce make_red(stag_engine* e, int kind, int S, double* partials = nullptr) {
     Reduce r{};
     r.partials = partials ? partials : e->partials;
     r.st = e->st;
     r.out = nullptr;
     r.st_out = nullptr;
     r.kind = kind;
-    r.nparts = (int)num_chunks(e->Vh);
-    return r;
-}
-
-// A reduction produced by a vector kernel: one partial per block of kBlock
-// sites (block_partials) instead of one per 64-site chunk.
-Reduce make_red_vec(stag_engine* e, int kind, double* partials = nullptr) {
-    Reduce r = make_red(e, kind, partials);
-    r.nparts = (int)vec_blocks(e->Vh);
+    r.nparts = (int)hop_blocks(e->Vh, S);
+    r.sub = S;
     return r;
 }
 
@@ -252,7 +256,7 @@ hipError_t hop(const Ctx& c, int prec, int stage, int epi, const void* in, void*
     const HopTune& t = prec == P64 && e->prec != P64 ? e->tune_64 : e->tune_lo;
     const int S = stage == 1 ? t.S1 : t.S2;
     const size_t rs = spinor_rhs_bytes(prec, e->Vh);
-    Reduce red = make_red(e, kind, o.partials);
+    Reduce red = make_red(e, kind, S, o.partials);
     RhsState* st = o.st ? o.st : e->st;
     const int p_out = stage == 1 ? 1 : 0;
     const int kk = prec == e->prec && run == F_ACTIVE ? (stage == 1 ? KK_HOP1 : KK_HOP2)
@@ -279,7 +283,7 @@ hipError_t vec(const Ctx& c, int prec, int op, std::initializer_list<std::pair<v
     a.st = o.st ? o.st : e->st;
     a.run_mask = run;
     a.swizzle = e->tune_lo.swizzle;
-    a.red = make_red_vec(e, kind, o.partials);
+    a.red = make_red(e, kind, 1, o.partials);
     if (o.fin) a.fin = *o.fin;
     const int kk = op == OP_UPD_CG || op == OP_UPD_MIXED ? KK_UPDATE : KK_OTHER;
     hipError_t err = timed_launch(c, kk, [&]() { return launch_vec(prec, c.nk, op, a, c.is); });
@@ -311,10 +315,10 @@ hipError_t enqueue_iterations_xpay(const Ctx& c, int K) {
     void* r = mixed ? e->rs : e->r64;
     const size_t rs = mixed ? e->rsP : e->rs64;
     const bool fuse = fuse_finalize(e, c.nk);
-    Reduce pend_r = make_red_vec(e, kind_r, e->partials1);
+    Reduce pend_r = make_red(e, kind_r, 1, e->partials1);
     pend_r.st = e->st1;
     pend_r.st_out = e->st;
-    Reduce pend_a = make_red(e, FIN_ALPHA, e->partials);
+    Reduce pend_a = make_red(e, FIN_ALPHA, e->tune_lo.S2, e->partials);
     pend_a.st = e->st;
     pend_a.st_out = e->st1;
     hipError_t err;
@@ -390,10 +394,10 @@ hipError_t enqueue_iterations(const Ctx& c, int K) {
     void* r = mixed ? e->rs : e->r64;
     const bool fuse = fuse_finalize(e, c.nk);
     if (separate_xpay(e, c.nk)) return enqueue_iterations_xpay(c, K);
-    Reduce pend_r = make_red_vec(e, kind_r, e->partials1);
+    Reduce pend_r = make_red(e, kind_r, 1, e->partials1);
     pend_r.st = e->st1;
     pend_r.st_out = e->st;
-    Reduce pend_a = make_red(e, FIN_ALPHA, e->partials);
+    Reduce pend_a = make_red(e, FIN_ALPHA, e->tune_lo.S2, e->partials);
     pend_a.st = e->st;
     pend_a.st_out = e->st1;
     hipError_t err;
@@ -455,7 +459,7 @@ hipError_t enqueue_update(const Ctx& c) {
     if (c.variant == MIXED_FOLD_ONLY) {
         if ((err = vec(c, e->prec, OP_FOLD, {{e->x64, e->rs64}, {e->y32, e->rs32}}, FIN_STORE, run)))
             return err;
-        Reduce gw = make_red(e, FIN_FOLD);
+        Reduce gw = make_red(e, FIN_FOLD, 1);
         gw.nparts = 0;  // a state transition: nothing to sum
         if ((err = timed_launch(c, KK_OTHER, [&]() { return launch_finalize(c.nk, gw, run, c.is); })))
             return err;
@@ -670,7 +674,7 @@ int run_start_slots(EngineRun& R, const std::vector<SlotInit>& slots) {
         RCK(vec(c, P64, OP_START, {{e->r64, e->rs64}, {e->d64, e->rs64}, {nullptr, 0}, {nullptr, 0}},
                 FIN_STORE, F_NEW));
     }
-    Reduce act = make_red(e, FIN_ACTIVATE);
+    Reduce act = make_red(e, FIN_ACTIVATE, 1);
     act.nparts = 0;  // a state transition: nothing to sum
     RCK(timed_launch(c, KK_OTHER, [&]() { return launch_finalize(c.nk, act, F_NEW, c.is); }));
     return STAG_OK;
@@ -708,6 +712,87 @@ static int get_graph(EngineRun& R, int nk, int K, hipGraphExec_t* out) {
     return STAG_OK;
 }
 
+// ------------------------------------------------------------------ resident iterations
+
+// Iterations per launch of the resident kernel: a fix-up comes due every few
+// tens of iterations in mixed CG, so this only bounds how long one launch
+// keeps the device to itself (about 10 us an iteration).
+constexpr int kPersistIters = 1024;
+// Rounds (one launch and its fix-up) between polls.
+constexpr int kPersistRounds = 3;
+// Longest wait inside the resident kernel, ticks of 10 ns: blocks that are not
+// resident yet wait for other streams' kernels to end, nothing else.
+constexpr long long kPersistLimit = 200000000;  // 2 s
+
+// One resident kernel at a time per device and process: two of them, each
+// holding part of the compute units, would wait for each other.
+static std::mutex& persist_mutex(int device) {
+    static std::mutex mu[64];
+    return mu[device & 63];
+}
+
+// Lanes per site of the resident kernel for n right-hand sides, 0: not here
+// (the groups of blocks have to be resident together, one block per compute
+// unit). Two lanes where they fit (8^4, us per iteration with 1 / 2 / 4 lanes: fp32
+// 8.7 / 8.0 / 10.0, fp64 - / 10.8 / 11.9, fp16 11.2 / 9.9 / 10.5; fewer blocks make
+// an exchange shorter, more lanes a wavefront's products); fp64 full links of
+// two pairs and both parities do not fit in registers, four lanes are faster
+// until the blocks run out (12^4 13.0 against 14.4). One lane for the rest, where
+// the kernel per stage is still slower (16^3 x 32, us per iteration: fp32 22.5
+// against 14.1, full links 26.1 against 21.5, fp16 19.5 against 16.8).
+static int persist_lanes(const stag_engine* e, int n) {
+    if (!e->ex) return 0;
+    const bool wide = e->prec == P64 && !e->gauge->r12;
+    const int order[3] = {wide ? 4 : 2, wide ? 2 : 1, 0};
+    for (int k = 0; order[k]; ++k) {
+        if (order[k] == 1 && e->prec == P64) break;  // no such kernel: registers
+        const uint32_t blocks = hop_blocks(e->Vh, order[k]);
+        if (blocks <= (uint32_t)kPersistBlocks && blocks * (uint32_t)n <= (uint32_t)e->ctx->cus)
+            return order[k];
+    }
+    return 0;
+}
+
+static int enqueue_persist_rounds(EngineRun& R, int nk) {
+    stag_engine* e = R.e;
+    const stag_gauge* g = e->gauge;
+    const int P = e->prec;
+    const bool mixed = P != P64;
+    PersistArgs a{};
+    for (int q = 0; q < 2; ++q) {
+        a.G[q] = g->G[P][q];
+        a.gscale[q] = P == P16S ? g->gscale[q] : nullptr;
+    }
+    a.g = g->g;
+    a.d = mixed ? e->d : e->d64;
+    a.t = mixed ? e->t : e->t64;
+    a.t2 = mixed ? e->Ad : e->Ad64;
+    a.r = mixed ? e->rs : e->r64;
+    a.y = mixed ? e->y32 : e->x64;
+    a.rsP = mixed ? e->rsP : e->rs64;
+    a.rsY = mixed ? e->rs32 : e->rs64;
+    a.st = e->st;
+    a.ex = e->ex;
+    a.abort = (int*)(e->st + e->N);
+    a.nrhs = R.nrhs;
+    a.blocks = (int)hop_blocks(e->Vh, R.persist);
+    a.one_xcd = a.blocks * ((R.nrhs + 7) / 8) <= 32;
+    a.max_iters = kPersistIters;
+    a.limit = kPersistLimit;
+    Ctx c{e, Issue{R.s}, nk, false, R.variant};
+    for (int k = 0; k < kPersistRounds; ++k) {
+        if (e->tag < 2 || e->tag > (1u << 30)) {
+            RCK(hipMemsetAsync(e->ex, 0, ex_bytes(e->N), R.s));
+            e->tag = 2;
+        }
+        a.tag = e->tag;
+        e->tag += 2u * kPersistIters + 2;
+        RCK(launch_persist(P, R.persist, g->r12, a, R.s));
+        RCK(mixed ? enqueue_update(c) : enqueue_check(c));
+    }
+    return STAG_OK;
+}
+
 // Enqueue one block (K iterations with fix-ups, R.K when K is 0) for the
 // busy slots, then the poll of the state.
 int run_enqueue_block(EngineRun& R, int K) {
@@ -716,7 +801,10 @@ int run_enqueue_block(EngineRun& R, int K) {
     const int k = K > 0 ? K : R.K;
     const long long j = R.launched;
     const int buf = (int)(j % 2);
-    if (R.use_graph) {
+    if (R.persist) {
+        int rc = enqueue_persist_rounds(R, nk);
+        if (rc) return rc;
+    } else if (R.use_graph) {
         hipGraphExec_t exec = nullptr;
         int rc = get_graph(R, nk, k, &exec);
         if (rc) return rc;
@@ -725,7 +813,7 @@ int run_enqueue_block(EngineRun& R, int K) {
         Ctx c{e, Issue{R.s}, nk, R.timed, R.variant};
         RCK(enqueue_block(c, k, R.F));
     }
-    RCK(hipMemcpyAsync(e->host[buf], e->st, state_bytes(e->N), hipMemcpyDeviceToHost, R.s));
+    RCK(hipMemcpyAsync(e->host[buf], e->st, state_bytes(e->N) + kAbortBytes, hipMemcpyDeviceToHost, R.s));
     RCK(hipEventRecord(e->ev[buf], R.s));
     R.launched = j + 1;
     return STAG_OK;
@@ -772,22 +860,16 @@ void fill_stats(const RhsState& s, double secs, int inner_prec, stag_cg_stats* o
 
 // ------------------------------------------------------------------ one-shot solve
 
-// Where one workgroup per right-hand side (tiny.hip) beats the kernel-per-
-// stage solver (measured, 1 and 8 RHS): one pass of four lanes per site
-// covers the lattice (128 sites per parity, 4^4: 7.3 against 7.8 ms for a
-// 1e-10 fp64 solve, 5.2 against 7.4 ms fp32, and 3.5-5x with 8 RHS), or a
-// batch of several right-hand sides on up to 648 sites (6^4: 8 RHS in 51
-// against 104 ms fp32, 87 against 104 ms fp64). An iteration costs a few
-// microseconds of barriers and memory round trips whatever the size, so
-// single solves of 6^4 and anything on 8^4 are faster with a kernel per
-// stage.
+// Lattices that one pass of four lanes per site covers (128 sites per parity,
+// 4^4) are solved by one workgroup per right-hand side (tiny.hip), whose
+// barriers stay inside a compute unit; larger ones by a group of workgroups
+// (persist.hip).
 constexpr uint32_t kTinySitesOnePass = 128;
-constexpr uint32_t kTinySitesBatch = 648;
 
-static bool tiny_solve_eligible(const stag_engine* e, int n, const stag_cg_params& p) {
+static bool tiny_solve_eligible(const stag_engine* e, const stag_cg_params& p) {
     const bool variant_ok = e->prec == P64 || p.mixed_variant == MIXED_CARRY ||
                             p.mixed_variant == MIXED_RESTART;
-    const bool size_ok = e->Vh <= kTinySitesOnePass || (n >= 2 && e->Vh <= kTinySitesBatch);
+    const bool size_ok = e->Vh <= kTinySitesOnePass;
     return p.small_lattice != 0 && size_ok && e->gauge->npairs == 4 && !p.use_x0 && variant_ok &&
            !e->ctx->timing.on;
 }
@@ -895,7 +977,7 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     const int K = p.graph_k > 0 ? p.graph_k : default_graph_k(e->Vh);
     RCK(hipMemcpy2DAsync(e->b64, e->rs64, b64, b_rs, e->rs64, n, hipMemcpyDeviceToDevice, stream));
     std::vector<RhsState> fin(n);
-    if (tiny_solve_eligible(e, n, p)) {
+    if (tiny_solve_eligible(e, p)) {
         int rc = tiny_solve(e, n, mass, p, escalating, stream, fin);
         if (rc) return rc;
         return engine_solve_finish(e, n, x_out, x_rs, stats, stream, fin, t0);
@@ -903,6 +985,13 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     EngineRun R;
     run_init(R, e, stream, e->b64, e->rs64, K, p.use_graph != 0);
     R.variant = e->prec != P64 ? p.mixed_variant : MIXED_CARRY;
+    // small lattices: the iterations in a resident kernel, unless another solve
+    // of this process has one on the device (the results are the same bits)
+    std::unique_lock<std::mutex> resident(persist_mutex(e->ctx->device), std::defer_lock);
+    if (p.small_lattice != 0 && R.use_graph && (R.persist = persist_lanes(e, n)) != 0 &&
+        !resident.try_lock())
+        R.persist = 0;
+    R.nrhs = n;
     std::vector<SlotInit> slots(n);
     for (int r = 0; r < n; ++r) {
         slots[r] = SlotInit{r, mass[r], p};
@@ -927,6 +1016,17 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
         const RhsState* h = nullptr;
         rc = run_process_poll(R, true, &h);
         if (rc) return rc;
+        if (R.persist && *(const int*)(h + e->N) != 0) {
+            // a wait of the resident kernel ran out (another process on the
+            // device): start over with a kernel per stage
+            RCK(hipStreamSynchronize(stream));
+            RCK(hipMemsetAsync(e->st + e->N, 0, kAbortBytes, stream));
+            e->tag = 0;
+            resident.unlock();
+            stag_cg_params q = p;
+            q.small_lattice = 0;
+            return engine_solve(e, n, mass, b64, b_rs, x_out, x_rs, q, stats, stream, escalating);
+        }
         bool all_terminal = true;
         for (int r = 0; r < n; ++r)
             if (!flags_terminal(h[r].flags)) all_terminal = false;
@@ -1003,16 +1103,16 @@ int time_iteration_kernels(stag_engine* e, const HopTune& t, int nrhs, int reps,
     }
     const bool mixed = prec != P64;
     const bool fuse = fuse_finalize(e, N);
-    Reduce pend_r = make_red_vec(e, FIN_STORE, e->partials1);
+    Reduce pend_r = make_red(e, FIN_STORE, 1, e->partials1);
     pend_r.st = e->st1;
     pend_r.st_out = e->st;
     pend_r.out = sink;
-    Reduce pend_a = make_red(e, FIN_STORE, e->partials);
+    Reduce pend_a = make_red(e, FIN_STORE, t.S2, e->partials);
     pend_a.st = e->st;
     pend_a.st_out = e->st1;
     pend_a.out = sink;
     auto one = [&](int which, const Issue& is) -> hipError_t {
-        Reduce red = make_red(e, FIN_STORE);
+        Reduce red = make_red(e, FIN_STORE, t.S2);
         const size_t rs = mixed ? e->rsP : e->rs64;
         void* dd = mixed ? e->d : e->d64;
         void* rr = mixed ? e->rs : e->r64;
@@ -1051,7 +1151,7 @@ int time_iteration_kernels(stag_engine* e, const HopTune& t, int nrhs, int reps,
         a.st = e->st;
         a.run_mask = F_ACTIVE;
         a.swizzle = t.swizzle;
-        a.red = make_red_vec(e, FIN_STORE, e->partials1);
+        a.red = make_red(e, FIN_STORE, 1, e->partials1);
         if (fuse) a.fin = pend_a;
         return launch_vec(prec, N, mixed ? OP_UPD_MIXED : OP_UPD_CG, a, is);
     };

@@ -18,8 +18,7 @@ namespace stag {
 // order by thread 0. Every thread gets the result.
 __device__ __forceinline__ double tiny_block_sum(double v, double* lds) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = wave_butterfly(v);
     if (lane == 0) lds[wave] = v;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -1,0 +1,103 @@
+"""Solves whose iterations run in the resident kernel (small lattices) against
+the kernel-per-stage solver: the stages, their rounding and the reduction
+order are the same, so the iterates are the same bits."""
+
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_common import links, log, oracle_apply_A
+
+pytestmark = pytest.mark.gpu
+
+# sites per parity: 192 (part of a block), 648 (a last wavefront of 8 sites), 2048, 3360,
+# 16384 / 32768 / 65536 (the most for four, two and one lanes per site), and two above
+LATTICES = [(4, 4, 4, 6), (6, 6, 6, 6), (8, 8, 8, 8), (8, 6, 10, 14), (16, 16, 16, 8),
+            (16, 16, 16, 16), (16, 16, 16, 18), (16, 16, 16, 32)]
+
+
+@pytest.fixture(scope="module")
+def stag():
+    import paper_1111_0125_amd as s
+    return s
+
+
+@pytest.fixture(scope="module")
+def ctx(stag):
+    c = stag.Context(0)
+    yield c
+    c.close()
+
+
+def both(stag, ctx, g, b, masses, x0=None, **kw):
+    n = b.shape[0]
+    fb = ctx.field(g, 0, "f64", n).load(b)
+    fx = ctx.field(g, 0, "f64", n)
+    got = []
+    for small in (True, False):
+        if x0 is not None:
+            fx.load(x0)
+        rc, st = stag.stag_cg_solve(ctx, g, masses, fb, fx,
+                                    stag.cg_params(small_lattice=small, use_x0=x0 is not None, **kw))
+        got.append((rc, [(s["iters"], s["reliable_updates"], s["restarts"], s["true_rel_res"]) for s in st],
+                    fx.store()))
+    fb.destroy()
+    fx.destroy()
+    return got
+
+
+@pytest.mark.parametrize("L", LATTICES)
+@pytest.mark.parametrize("inner", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("r12", [False, True])
+def test_resident_equals_kernel_per_stage(stag, ctx, L, inner, r12):
+    vh = L[0] * L[1] * L[2] * L[3] // 2
+    U = links(L, "exp", 51, 0.3)
+    g = ctx.gauge(L, U, precisions=("f64", "f32", "f16s"), r12=r12)
+    n = 1 if vh > 4096 else 3
+    masses = [0.2, 0.3, 0.25][:n]
+    b = synth.gaussian_rhs(L, n, 52)
+    print("resident", L, inner, r12, n, flush=True)
+    (rc1, st1, x1), (rc2, st2, x2) = both(stag, ctx, g, b, masses, tol=1e-9, inner=inner)
+    log("resident", L, inner, r12, st1)
+    assert rc1 == 0 and rc2 == 0
+    assert st1 == st2
+    assert np.array_equal(x1, x2)
+    if vh <= 4096:
+        r = b - oracle_apply_A(U, x1, L, masses)
+        assert max(np.linalg.norm(r[k]) / np.linalg.norm(b[k]) for k in range(n)) <= 1e-9
+    g.destroy()
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+@pytest.mark.parametrize("n", [2, 9, 16])
+def test_resident_blocks_start_guess_and_cap(stag, ctx, inner, n):
+    """Several right-hand sides (each its own group of blocks), a zero one, a
+    start from a guess, and the iteration cap."""
+    L = (6, 6, 6, 6)
+    U = links(L, "haar", 53)
+    g = ctx.gauge(L, U, precisions=("f64", "f32"))
+    masses = [0.1 + 0.02 * k for k in range(n)]
+    b = synth.gaussian_rhs(L, n, 54)
+    b[n // 2] = 0.0
+    x0 = synth.gaussian_rhs(L, n, 55)
+    for kw in (dict(), dict(x0=x0), dict(max_iter=7, x0=x0)):
+        print("resident block", inner, n, sorted(kw), flush=True)
+        (rc1, st1, x1), (rc2, st2, x2) = both(stag, ctx, g, b, masses, tol=1e-10, inner=inner, **kw)
+        assert rc1 == rc2 and st1 == st2
+        assert np.array_equal(x1, x2)
+        if "max_iter" not in kw:
+            assert rc1 == 0
+    g.destroy()
+
+
+@pytest.mark.parametrize("variant", ["restart", "reliable", "fold_only"])
+def test_resident_mixed_variants(stag, ctx, variant):
+    L = (8, 8, 4, 8)
+    U = links(L, "exp", 56, 0.4)
+    g = ctx.gauge(L, U, precisions=("f64", "f32"))
+    b = synth.gaussian_rhs(L, 1, 57)
+    (rc1, st1, x1), (rc2, st2, x2) = both(stag, ctx, g, b, [0.1], tol=1e-9, inner="f32",
+                                          mixed_variant=variant, max_iter=400)
+    assert rc1 == rc2 and st1 == st2
+    assert np.array_equal(x1, x2)
+    g.destroy()
