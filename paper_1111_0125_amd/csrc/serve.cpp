@@ -367,8 +367,12 @@ static void scheduler(Serve* S) {
             std::unique_lock<std::mutex> lk(S->mu);
             if (S->stop) break;
             drop_batches(S);
+            // nothing to do until a submit, unless a ticket's last result copy
+            // is still on its way (a wait here would keep the finished ticket
+            // pending for its whole length)
             bool any_busy = false;
             for (Batch* b : S->batches) any_busy |= b->busy > 0;
+            for (auto& kv : S->tickets) any_busy |= kv.second->finishing && !kv.second->done;
             if (S->queue.empty() && !any_busy) {
                 S->cv.wait_for(lk, std::chrono::milliseconds(50));
                 if (S->stop) break;
