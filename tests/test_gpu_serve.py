@@ -217,7 +217,7 @@ def test_finished_request_is_not_held_back(stag):
     """A lone small request is reported once its result copy is done, not at
     the scheduler's next idle wake-up (50 ms): a 4^4 solve takes about 10 ms."""
     L = (4, 4, 4, 4)
-    U = links(L, "haar", 61)
+    U = synth.haar_links(L, 61)
     with stag.Context(0) as ctx:
         g = ctx.gauge(L, U, precisions=("f64", "f32"))
         lat = []
