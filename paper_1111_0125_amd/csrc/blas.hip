@@ -264,6 +264,7 @@ static hipError_t run_vec(int N, int op, const VecArgs& a, const Issue& is) {
     switch (N) {
         case 1: return run_vec_n<P, 1>(op, a, is);
         case 2: return run_vec_n<P, 2>(op, a, is);
+        case 3: return run_vec_n<P, 3>(op, a, is);
         case 4: return run_vec_n<P, 4>(op, a, is);
         case 8: return run_vec_n<P, 8>(op, a, is);
         case 12: return run_vec_n<P, 12>(op, a, is);
@@ -301,6 +302,7 @@ hipError_t launch_finalize(int N, const Reduce& R, unsigned run_mask, const Issu
     switch (N) {
         case 1: return issue_finalize<1>(R, run_mask, is);
         case 2: return issue_finalize<2>(R, run_mask, is);
+        case 3: return issue_finalize<3>(R, run_mask, is);
         case 4: return issue_finalize<4>(R, run_mask, is);
         case 8: return issue_finalize<8>(R, run_mask, is);
         case 12: return issue_finalize<12>(R, run_mask, is);

@@ -619,22 +619,10 @@ int stag_dslash(stag_ctx* ctx, const stag_gauge* g, const stag_field* in, stag_f
         return set_error(ctx, STAG_EINVAL, "stag_dslash: out parity must be 1 - in parity");
     DeviceGuard dg(ctx->device);
     hipStream_t s = pick_stream(ctx, stream);
-    const int N = pick_n(in->nrhs);
-    // process exactly nrhs blocks: spare slots of the N-kernel get no state
-    // and would be processed, so run in chunks of instantiated sizes
+    // exactly nrhs: a spare slot without state would be processed too
     int done = 0;
     while (done < in->nrhs) {
-        int n = in->nrhs - done;
-        int Nk = pick_n(n);
-        if (Nk > n) {
-            // largest instantiated size <= n
-            static const int ns[] = {16, 12, 8, 4, 2, 1};
-            for (int v : ns)
-                if (v <= n) {
-                    Nk = v;
-                    break;
-                }
-        }
+        const int Nk = fit_n(in->nrhs - done);
         HopTune t = get_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
         const char* ip = (const char*)in->data + (size_t)done * in->rs;
         char* op = (char*)out->data + (size_t)done * out->rs;
@@ -642,7 +630,6 @@ int stag_dslash(stag_ctx* ctx, const stag_gauge* g, const stag_field* in, stag_f
                                out->parity, nullptr, 0, nullptr, 0, nullptr, nullptr, 0, nullptr, Issue{s}));
         done += Nk;
     }
-    (void)N;
     return STAG_OK;
 }
 
@@ -652,14 +639,7 @@ static int apply_A_stages(stag_ctx* ctx, const stag_gauge* g, const double* mass
                           const stag_field* in, stag_field* out, void* t, hipStream_t s) {
     int done = 0;
     while (done < in->nrhs) {
-        int n = in->nrhs - done;
-        int Nk = 1;
-        static const int ns[] = {16, 12, 8, 4, 2, 1};
-        for (int v : ns)
-            if (v <= n) {
-                Nk = v;
-                break;
-            }
+        const int Nk = fit_n(in->nrhs - done);
         double m2[kMaxN] = {0};
         for (int r = 0; r < Nk; ++r) m2[r] = mass[done + r] * mass[done + r];
         HopTune tu = get_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);

@@ -26,7 +26,6 @@
 #ifndef HOP_NP
 #define HOP_NP 4
 #endif
-
 namespace stag {
 
 // What an operand is made of at one site: the stored input and, for a
@@ -100,6 +99,138 @@ __device__ __forceinline__ void pair_neighbours(const Geom& g, uint32_t s, int x
     } else {
         neighbours3(g, s, x, y, z, t, pr & 3, nf, nb);
     }
+}
+
+// Load a colour vector from field f (a kernel argument, so uniform): the
+// plane's address stays in scalar registers and the site is a 32-bit offset
+// to it (sites per parity below kHop32MaxSites).
+template <int P>
+__device__ __forceinline__ void load_site32(const void* f, uint32_t Vh, uint32_t s,
+                                            typename Real<P>::T (&re)[3],
+                                            typename Real<P>::T (&im)[3]) {
+    if constexpr (P == P16S) {
+        f16s_decode(*(const u4v*)((const char*)f + s * 16u), re, im);
+    } else {
+        using V = std::conditional_t<P == P64, d2v, f2v>;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const V v = *(const V*)((const char*)f + (size_t)c * Vh * sizeof(V) + s * (uint32_t)sizeof(V));
+            re[c] = v.x;
+            im[c] = v.y;
+        }
+    }
+}
+
+// Planes of at most 4 GiB (16 bytes a site), for the 32-bit offsets above.
+constexpr uint32_t kHop32MaxSites = 1u << 27;
+
+// Where hop_all serves: the default launch shape (four pairs per lane) and
+// blocks of up to 8; the improved operator's fp64 and fp32 blocks of 2 to 4 stay with
+// the branching loop (16^3 x 32 fp64 with 4 RHS: 50.9 / 41.8 us there, 53.1 / 46.6
+// here).
+template <int P, int S, int N, int NP>
+constexpr bool kUseHopAll = N > 1 && N <= 8 && S == NP / 4 && (NP == 4 || N == 8 || P == P16S);
+
+// The pair sums of several right-hand sides, all of them active, at output
+// site sl (every lane of the wavefront has one): the operands of right-hand
+// side and pair i + AHEAD are requested before the products of i, with no
+// branch per right-hand side in between, and the next pair's links before
+// this pair's products (8 RHS: three ahead and the links with them, which
+// leaves the registers). Stage 1 / stage 2 at 24^3 x 48 with 12-parameter links,
+// us, against the branching loop of k_hop below: fp32 with 4 RHS 42.2 / 46.6
+// (45.4 / 55.4), 8 RHS 65.1 / 79.3 (79.0 / 90.5); fp64 8 RHS 122.7 / 164.4 (177.1 /
+// 211.4), 2 and 4 the same; fp16 2 RHS 20.2 / 23.5 (25.8 / 28.1), 8 RHS 56.0 / 69.3
+// (76.7 / 75.6). fp32 with one request ahead: 4 RHS 43.5 / 49.2, 8 RHS 74.0 / 89.3.
+template <int P, int S, int N, int EPI, bool NT, int NP, bool R12, bool LAZY>
+__device__ __forceinline__ void hop_all(const HopArgs& a, uint32_t sl, int x, int y, int z, int t, int j,
+                                        const RhsState* ls, typename Real<P>::T (&ar)[N][3],
+                                        typename Real<P>::T (&ai)[N][3]) {
+    using T = typename Real<P>::T;
+    constexpr int B = NP / S;
+    constexpr int AHEAD = N >= 8 ? 3 : 2;
+    constexpr bool LINKS_AHEAD = N < 8;
+    const uint32_t Vh = a.g.Vh;
+    uint32_t nf[B], nb[B];
+    static_for<0, B>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        pair_neighbours<NP>(a.g, sl, x, y, z, t, j * B + k, nf[k], nb[k]);
+    });
+    struct Op {
+        T fr[3], fi[3], br[3], bi[3];
+        T gr[LAZY ? 3 : 1], gi[LAZY ? 3 : 1], hr[LAZY ? 3 : 1], hi[LAZY ? 3 : 1];
+    };
+    Op q[AHEAD];
+    auto request = [&](int i, Op& w) {
+        const int k = i / N, r = i % N;
+        const char* in_r = (const char*)a.in + (size_t)r * a.in_rs;
+        load_site32<P>(in_r, Vh, nf[k], w.fr, w.fi);
+        load_site32<P>(in_r, Vh, nb[k], w.br, w.bi);
+        if constexpr (LAZY) {
+            const char* z_r = (const char*)a.lazy_r + (size_t)r * a.lazy_r_rs;
+            load_site32<P>(z_r, Vh, nf[k], w.gr, w.gi);
+            load_site32<P>(z_r, Vh, nb[k], w.hr, w.hi);
+        }
+    };
+    PairRaw<P> lw;
+    load_pair_raw<P, NT, NP>(a.gauge, a.gscale, sl, j * B, R12, lw);
+    static_for<0, AHEAD>([&](auto ic) { request(decltype(ic)::value, q[decltype(ic)::value]); });
+    T pdr[3][N][3], pdi[3][N][3];
+    T lr[18], li[18];
+    PairScale<T> ps;
+    static_for<0, B * N>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, k = i / N, r = i % N;
+        if constexpr (r == 0) {
+            finish_pair<P>(R12, eta_sign((j * B + k) & 3, x, y, z), lw, lr, li, ps);
+            if constexpr (LINKS_AHEAD && k + 1 < B) {
+#pragma unroll
+                for (int e = 0; e < 18; ++e) asm volatile("" : "+v"(lr[e]), "+v"(li[e])::"memory");
+                load_pair_raw<P, NT, NP>(a.gauge, a.gscale, sl, j * B + k + 1, R12, lw);
+            }
+        }
+        Op& w = q[i % AHEAD];
+        T pr[3], pi[3];
+        if constexpr (LAZY) {
+            const T be = (T)ls[r].beta;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                w.fr[c] = fma(be, w.fr[c], w.gr[c]);
+                w.fi[c] = fma(be, w.fi[c], w.gi[c]);
+                w.br[c] = fma(be, w.br[c], w.hr[c]);
+                w.bi[c] = fma(be, w.bi[c], w.hi[c]);
+            }
+            round_site<P>(w.fr, w.fi);
+            round_site<P>(w.br, w.bi);
+        }
+        pair_start(lr, li, w.fr, w.fi, pr, pi);
+        pair_finish(lr, li, ps, w.br, w.bi, pr, pi);
+        // requests stay behind the products (an empty statement that uses them)
+        if constexpr (i + AHEAD < B * N || (!LINKS_AHEAD && r == N - 1 && k + 1 < B)) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) asm volatile("" : "+v"(pr[c]), "+v"(pi[c])::"memory");
+        }
+        if constexpr (!LINKS_AHEAD && r == N - 1 && k + 1 < B)
+            load_pair_raw<P, NT, NP>(a.gauge, a.gscale, sl, j * B + k + 1, R12, lw);
+        if constexpr (i + AHEAD < B * N) request(i + AHEAD, w);
+        // the balanced tree ((p0 + p1) + (p2 + p3)) + ...
+        constexpr int lvl = (k & 1) == 0 ? 0 : (k & 2) == 0 ? 1 : (k & 4) == 0 ? 2 : 3;
+#pragma unroll
+        for (int l = 0; l < lvl; ++l)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                pr[c] = pdr[l][r][c] + pr[c];
+                pi[c] = pdi[l][r][c] + pi[c];
+            }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if constexpr (k == B - 1) {
+                ar[r][c] = pr[c];
+                ai[r][c] = pi[c];
+            } else {
+                pdr[lvl][r][c] = pr[c];
+                pdi[lvl][r][c] = pi[c];
+            }
+        }
+    });
 }
 
 template <int P, int S, int N, int EPI, bool NT, int NP>
@@ -209,7 +340,32 @@ __global__ __launch_bounds__(kBlock) void k_hop(HopArgs a) {
             for (int l = 0; l < (LOGB > 0 ? LOGB : 1); ++l) pdr[l][r][c] = pdi[l][r][c] = T(0);
         }
 
-    if (valid && act) {
+    bool done = false;
+    if constexpr (kUseHopAll<P, S, N, NP>) {
+        // every right-hand side active (the fp64 fix-ups gather x + y: below)
+        if (act == (1u << N) - 1u && Vh < kHop32MaxSites && !(EPI == EPI_PLAIN && a.lazy_y)) {
+            const uint32_t sl = valid ? s : Vh - 1;
+            int cx, cy, cz, ct;
+            site_coords(a.g, sl, a.p_out, cx, cy, cz, ct);
+            auto all = [&](auto r12c, auto lazyc) {
+                hop_all<P, S, N, EPI, NT, NP, decltype(r12c)::value, decltype(lazyc)::value>(
+                    a, sl, cx, cy, cz, ct, j, ls, ar, ai);
+            };
+            if constexpr (EPI == EPI_PLAIN && N < 8) {
+                if (lazy_nb) {
+                    if (r12) all(std::true_type(), std::true_type());
+                    else all(std::false_type(), std::true_type());
+                    done = true;
+                }
+            }
+            if (!lazy_nb) {
+                if (r12) all(std::true_type(), std::false_type());
+                else all(std::false_type(), std::false_type());
+                done = true;
+            }
+        }
+    }
+    if (valid && act && !done) {
         // Each hop pair contributes p = F chi(x+h) + B chi(x-h), accumulated
         // from zero; the pairs are summed along a balanced binary tree
         // ((p0 + p1) + (p2 + p3)) + ..., lane-locally over the aligned block
@@ -402,26 +558,6 @@ __global__ __launch_bounds__(kBlock) void k_hop(HopArgs a) {
 
 // ------------------------------------------------------------------ one right-hand side
 
-// Load a colour vector from field f (a kernel argument, so uniform): the
-// plane's address stays in scalar registers and the site is a 32-bit offset
-// to it (sites per parity below kHop1MaxSites).
-template <int P>
-__device__ __forceinline__ void load_site32(const void* f, uint32_t Vh, uint32_t s,
-                                            typename Real<P>::T (&re)[3],
-                                            typename Real<P>::T (&im)[3]) {
-    if constexpr (P == P16S) {
-        f16s_decode(*(const u4v*)((const char*)f + s * 16u), re, im);
-    } else {
-        using V = std::conditional_t<P == P64, d2v, f2v>;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const V v = *(const V*)((const char*)f + (size_t)c * Vh * sizeof(V) + s * (uint32_t)sizeof(V));
-            re[c] = v.x;
-            im[c] = v.y;
-        }
-    }
-}
-
 // Everything one hop pair reads: links, both neighbours, and with a deferred
 // direction their residuals.
 template <int P, bool LAZY>
@@ -605,7 +741,6 @@ __global__ __launch_bounds__(kBlock) void k_hop1(HopArgs a) {
 // full links at 32^3 x 64 (225 against 232 us), nothing with 12-parameter links
 // (160 us), and whole solves became slower (16^3 x 32 27.1 against 25.4 ms,
 // 24^3 x 48 full 136.5 against 134.7 ms).
-constexpr uint32_t kHop1MaxSites = 1u << 27;
 template <int P, int NP>
 constexpr bool kUseHop1 = P != P32 || NP == 8;
 
@@ -657,7 +792,7 @@ template <int P, int EPI>
 static hipError_t dispatch_epi(int S, int N, bool nt, const HopArgs& a, const Issue& is) {
     if (N == 1) {
         if constexpr (EPI != EPI_RESID && kUseHop1<P, HOP_NP>) {
-            if (nt && S == HOP_NP / 4 && !a.lazy_y && !a.gate && a.g.Vh < kHop1MaxSites &&
+            if (nt && S == HOP_NP / 4 && !a.lazy_y && !a.gate && a.g.Vh < kHop32MaxSites &&
                 !(EPI == EPI_XPAY && a.lazy_r) && !(a.fin.partials && (EPI != EPI_PLAIN || !a.lazy_r)))
                 return dispatch_hop1<P, EPI>(a, is);
         }
@@ -674,6 +809,7 @@ static hipError_t dispatch_epi(int S, int N, bool nt, const HopArgs& a, const Is
     }
     switch (N) {
         case 2: return run_block<P, EPI, 2>(S, a, is);
+        case 3: return run_block<P, EPI, 3>(S, a, is);
         case 4: return run_block<P, EPI, 4>(S, a, is);
         case 8: return run_block<P, EPI, 8>(S, a, is);
         case 12: return run_block<P, EPI, 12>(S, a, is);

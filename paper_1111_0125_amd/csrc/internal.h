@@ -133,7 +133,14 @@ struct stag_engine {
     unsigned long long* ex = nullptr;
     uint32_t tag = 0;
     size_t bytes = 0;
-    std::map<long long, hipGraphExec_t> graphs;    // one block of work; key: (K, kernel N)
+    // one block of work of a group of slots; key: (K, variant, first slot, kernel N)
+    std::map<long long, hipGraphExec_t> graphs;
+    struct Branch {
+        hipStream_t s = nullptr;
+        hipEvent_t done = nullptr;
+    };
+    std::vector<Branch> gstreams;   // streams of the second and further groups
+    hipEvent_t gfork = nullptr;
     stag::HopTune tune_lo, tune_64;
 };
 

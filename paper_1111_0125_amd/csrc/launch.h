@@ -131,11 +131,15 @@ hipError_t launch_export(int prec, const void* src, size_t src_rs, void* dst_dev
 // The right-hand-side counts the kernels are instantiated for; a batch of n
 // runs in the smallest of these >= n with the spare slots inactive.
 inline int pick_n(int n) {
-    static const int ns[] = {1, 2, 4, 8, 12, 16};
+    static const int ns[] = {1, 2, 3, 4, 8, 12, 16};
     for (int v : ns)
         if (v >= n) return v;
     return -1;
 }
+// The largest kernel block for the first of n right-hand sides without spare
+// slots: operator calls of more than 8 run as blocks of 8 and the rest (per
+// right-hand side a block of 12 or 16 costs more than one of 8).
+inline int fit_n(int n) { return n >= 8 ? 8 : n >= 4 ? 4 : n; }
 
 constexpr int kBlock = 256;  // threads per block of every kernel
 

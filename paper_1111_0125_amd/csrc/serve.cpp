@@ -525,7 +525,7 @@ int stag_solver_config(stag_ctx* ctx, int slots_per_batch, int graph_k, int queu
     std::lock_guard<std::mutex> lk(S->mu);
     if (S->started)
         return set_error(ctx, STAG_EBUSY, "stag_solver_config: serving already started");
-    S->slots = pick_n(slots_per_batch);
+    S->slots = pick_n(slots_per_batch == 3 ? 4 : slots_per_batch);
     S->graph_k = graph_k;
     S->queue_cap = (size_t)queue_cap;
     return STAG_OK;

@@ -53,6 +53,11 @@ void engine_destroy(stag_engine* e) {
         if (e->ev[i]) (void)hipEventDestroy(e->ev[i]);
     }
     if (e->hstage) (void)hipHostFree(e->hstage);
+    for (auto& br : e->gstreams) {
+        if (br.done) (void)hipEventDestroy(br.done);
+        (void)hipStreamDestroy(br.s);
+    }
+    if (e->gfork) (void)hipEventDestroy(e->gfork);
     ctx->used.fetch_sub(e->bytes);
     delete e;
 }
@@ -548,22 +553,33 @@ int group_size(const stag_engine* e, int nk) {
     return nk <= kSmallGroupRhs && e->Vh < kSmallGroupSites ? kSmallGroup : kMaxGroup;
 }
 
-// One block (K iterations with their fix-ups) for the slots below nk. In a
-// graph the groups are independent branches.
+// One block (K iterations with their fix-ups) of the slots [g0, g0 + nk).
+hipError_t enqueue_slots(const Ctx& c, int g0, int nk, int K, int F) {
+    if (g0 == 0 && nk == c.nk) return enqueue_block_group(c, K, F);
+    stag_engine v;
+    slot_view(c.e, g0, nk, &v);
+    Ctx cg = c;
+    cg.e = &v;
+    cg.nk = nk;
+    return enqueue_block_group(cg, K, F);
+}
+
+// Kernel groups of the slots below nk: group i starts at slot i * gs.
+int group_count(const stag_engine* e, int nk) {
+    const int gs = group_size(e, nk);
+    return (nk + gs - 1) / gs;
+}
+int group_slots(const stag_engine* e, int nk, int i) {
+    const int gs = group_size(e, nk);
+    return nk <= gs ? nk : pick_n(std::min(gs, nk - i * gs));
+}
+
+// One block for the slots below nk, group after group.
 hipError_t enqueue_block(const Ctx& c, int K, int F) {
-    const int gs = group_size(c.e, c.nk);
-    if (c.nk <= gs) return enqueue_block_group(c, K, F);
     hipError_t err = hipSuccess;
-    for (int g0 = 0; g0 < c.nk && err == hipSuccess; g0 += gs) {
-        const int nk = pick_n(std::min(gs, c.nk - g0));
-        stag_engine v;
-        slot_view(c.e, g0, nk, &v);
-        Ctx cg = c;
-        cg.e = &v;
-        cg.nk = nk;
-        if (c.is.gb) c.is.gb->last = nullptr;  // a new branch from the graph's start
-        err = enqueue_block_group(cg, K, F);
-    }
+    const int gs = group_size(c.e, c.nk);
+    for (int i = 0; i < group_count(c.e, c.nk) && err == hipSuccess; ++i)
+        err = enqueue_slots(c, i * gs, group_slots(c.e, c.nk, i), K, F);
     return err;
 }
 
@@ -680,12 +696,13 @@ int run_start_slots(EngineRun& R, const std::vector<SlotInit>& slots) {
     return STAG_OK;
 }
 
-// The graph of one block of work (K iterations with their fix-ups) for
-// kernel block size nk, built node by node on first use and kept. Every
-// buffer it uses belongs to the engine, so it serves every later block.
-static int get_graph(EngineRun& R, int nk, int K, hipGraphExec_t* out) {
+// The graph of one block of work (K iterations with their fix-ups) for the
+// nk slots from g0 on, built node by node on first use and kept: one chain of
+// kernels. Every buffer it uses belongs to the engine, so it serves every
+// later block.
+static int get_graph(EngineRun& R, int g0, int nk, int K, hipGraphExec_t* out) {
     stag_engine* e = R.e;
-    const long long key = ((long long)K << 16) | ((long long)R.variant << 8) | (long long)nk;
+    const long long key = ((long long)K << 24) | ((long long)R.variant << 16) | (g0 << 8) | nk;
     auto it = e->graphs.find(key);
     if (it != e->graphs.end()) {
         *out = it->second;
@@ -696,8 +713,8 @@ static int get_graph(EngineRun& R, int nk, int K, hipGraphExec_t* out) {
     if (err == hipSuccess) {
         Issue is;
         is.gb = &gb;
-        Ctx c{e, is, nk, false, R.variant};
-        err = enqueue_block(c, K, R.F);
+        Ctx c{e, is, g0 == 0 ? nk : 0, false, R.variant};
+        err = enqueue_slots(c, g0, nk, K, R.F);
     }
     hipGraphExec_t exec = nullptr;
     if (err == hipSuccess) err = hipGraphInstantiate(&exec, gb.graph, nullptr, nullptr, 0);
@@ -709,6 +726,35 @@ static int get_graph(EngineRun& R, int nk, int K, hipGraphExec_t* out) {
     }
     e->graphs.emplace(key, exec);
     *out = exec;
+    return STAG_OK;
+}
+
+// One block as graphs: the first group's on the run's stream, each further
+// group's on a stream of the engine that starts after the run's stream and is
+// waited for by it, so the groups overlap on the device.
+static int launch_block_graphs(EngineRun& R, int nk, int K) {
+    stag_engine* e = R.e;
+    const int n = group_count(e, nk), gs = group_size(e, nk);
+    if (n > 1) {
+        while ((int)e->gstreams.size() < n - 1) {
+            stag_engine::Branch br;
+            RCK(hipStreamCreateWithFlags(&br.s, hipStreamNonBlocking));
+            e->gstreams.push_back(br);
+            RCK(hipEventCreateWithFlags(&e->gstreams.back().done, hipEventDisableTiming));
+        }
+        if (!e->gfork) RCK(hipEventCreateWithFlags(&e->gfork, hipEventDisableTiming));
+        RCK(hipEventRecord(e->gfork, R.s));
+    }
+    for (int i = n - 1; i >= 0; --i) {
+        hipGraphExec_t exec = nullptr;
+        int rc = get_graph(R, i * gs, group_slots(e, nk, i), K, &exec);
+        if (rc) return rc;
+        const hipStream_t s = i == 0 ? R.s : e->gstreams[i - 1].s;
+        if (i > 0) RCK(hipStreamWaitEvent(s, e->gfork, 0));
+        RCK(hipGraphLaunch(exec, s));
+        if (i > 0) RCK(hipEventRecord(e->gstreams[i - 1].done, s));
+    }
+    for (int i = 1; i < n; ++i) RCK(hipStreamWaitEvent(R.s, e->gstreams[i - 1].done, 0));
     return STAG_OK;
 }
 
@@ -805,10 +851,8 @@ int run_enqueue_block(EngineRun& R, int K) {
         int rc = enqueue_persist_rounds(R, nk);
         if (rc) return rc;
     } else if (R.use_graph) {
-        hipGraphExec_t exec = nullptr;
-        int rc = get_graph(R, nk, k, &exec);
+        int rc = launch_block_graphs(R, nk, k);
         if (rc) return rc;
-        RCK(hipGraphLaunch(exec, R.s));
     } else {
         Ctx c{e, Issue{R.s}, nk, R.timed, R.variant};
         RCK(enqueue_block(c, k, R.F));
