@@ -535,22 +535,22 @@ void slot_view(const stag_engine* e, int g0, int nk, stag_engine* v) {
     v->tune_64 = get_tune(e->ctx, P64, nk, e->Vh, e->gauge->npairs);
 }
 
-// Block kernels serve at most this many right-hand sides: per right-hand
-// side an iteration costs less with 8 per kernel than with 12 or 16 (whose
-// neighbour gathers miss the caches more), so larger batches run as groups
-// of 8 (and the rest), each its own chain of kernels.
-constexpr int kMaxGroup = 8;
-// The groups' chains overlap on the device. Below kSmallGroupSites sites per
-// parity a kernel leaves room for another chain's, and blocks of up to
-// kSmallGroupRhs right-hand sides run as groups of kSmallGroup: 8 and 12 RHS
-// 10-14 % faster per solve on 16^3 x 32 and 7-10 % on 24^3 x 48 than as 8 and
-// 8 + 4; on 32^3 x 64 and for 16 RHS groups of 8 measured as fast or faster.
-constexpr int kSmallGroup = 4;
-constexpr int kSmallGroupRhs = 12;
-constexpr uint32_t kSmallGroupSites = 524288;
-
-int group_size(const stag_engine* e, int nk) {
-    return nk <= kSmallGroupRhs && e->Vh < kSmallGroupSites ? kSmallGroup : kMaxGroup;
+// Kernels serve groups of 8, 4, 3, 2 or 1 slots, each group its own chain, so
+// that no kernel has idle slots (its fast loop needs every one active) and none
+// more than 8 (per right-hand side an iteration costs less with 8 per kernel
+// than with 12 or 16, whose neighbour gathers miss the caches more). Below
+// kXpayMinSites sites per parity 5 to 8 slots run as two groups of 4, which
+// overlap (ms per solve, 16^3 x 32: 8 RHS 48.6 against 52.3 as one group, 5 RHS 42.2
+// against 51.3 as 4 + 1; on 24^3 x 48 8 RHS 415 against 350). 12 RHS as 8 + 4: 68.5
+// against 82.8 as three groups on 16^3 x 32, 501 against 506 on 24^3 x 48.
+struct Group {
+    int g0, n;
+};
+std::vector<Group> slot_groups(const stag_engine* e, int busy) {
+    if (busy > 4 && busy <= 8 && e->Vh < kXpayMinSites) return {{0, 4}, {4, 4}};
+    std::vector<Group> v;
+    for (int g0 = 0; g0 < busy; g0 += v.back().n) v.push_back({g0, fit_n(busy - g0)});
+    return v;
 }
 
 // One block (K iterations with their fix-ups) of the slots [g0, g0 + nk).
@@ -564,22 +564,11 @@ hipError_t enqueue_slots(const Ctx& c, int g0, int nk, int K, int F) {
     return enqueue_block_group(cg, K, F);
 }
 
-// Kernel groups of the slots below nk: group i starts at slot i * gs.
-int group_count(const stag_engine* e, int nk) {
-    const int gs = group_size(e, nk);
-    return (nk + gs - 1) / gs;
-}
-int group_slots(const stag_engine* e, int nk, int i) {
-    const int gs = group_size(e, nk);
-    return nk <= gs ? nk : pick_n(std::min(gs, nk - i * gs));
-}
-
-// One block for the slots below nk, group after group.
-hipError_t enqueue_block(const Ctx& c, int K, int F) {
+// One block for the slots below busy, group after group.
+hipError_t enqueue_block(const Ctx& c, int busy, int K, int F) {
     hipError_t err = hipSuccess;
-    const int gs = group_size(c.e, c.nk);
-    for (int i = 0; i < group_count(c.e, c.nk) && err == hipSuccess; ++i)
-        err = enqueue_slots(c, i * gs, group_slots(c.e, c.nk, i), K, F);
+    for (const Group& g : slot_groups(c.e, busy))
+        if (err == hipSuccess) err = enqueue_slots(c, g.g0, g.n, K, F);
     return err;
 }
 
@@ -732,9 +721,10 @@ static int get_graph(EngineRun& R, int g0, int nk, int K, hipGraphExec_t* out) {
 // One block as graphs: the first group's on the run's stream, each further
 // group's on a stream of the engine that starts after the run's stream and is
 // waited for by it, so the groups overlap on the device.
-static int launch_block_graphs(EngineRun& R, int nk, int K) {
+static int launch_block_graphs(EngineRun& R, int busy, int K) {
     stag_engine* e = R.e;
-    const int n = group_count(e, nk), gs = group_size(e, nk);
+    const std::vector<Group> groups = slot_groups(e, busy);
+    const int n = (int)groups.size();
     if (n > 1) {
         while ((int)e->gstreams.size() < n - 1) {
             stag_engine::Branch br;
@@ -747,7 +737,7 @@ static int launch_block_graphs(EngineRun& R, int nk, int K) {
     }
     for (int i = n - 1; i >= 0; --i) {
         hipGraphExec_t exec = nullptr;
-        int rc = get_graph(R, i * gs, group_slots(e, nk, i), K, &exec);
+        int rc = get_graph(R, groups[i].g0, groups[i].n, K, &exec);
         if (rc) return rc;
         const hipStream_t s = i == 0 ? R.s : e->gstreams[i - 1].s;
         if (i > 0) RCK(hipStreamWaitEvent(s, e->gfork, 0));
@@ -843,7 +833,7 @@ static int enqueue_persist_rounds(EngineRun& R, int nk) {
 // busy slots, then the poll of the state.
 int run_enqueue_block(EngineRun& R, int K) {
     stag_engine* e = R.e;
-    const int nk = pick_n(R.busy_hi > 0 ? R.busy_hi : 1);
+    const int busy = R.busy_hi > 0 ? R.busy_hi : 1, nk = pick_n(busy);
     const int k = K > 0 ? K : R.K;
     const long long j = R.launched;
     const int buf = (int)(j % 2);
@@ -851,11 +841,11 @@ int run_enqueue_block(EngineRun& R, int K) {
         int rc = enqueue_persist_rounds(R, nk);
         if (rc) return rc;
     } else if (R.use_graph) {
-        int rc = launch_block_graphs(R, nk, k);
+        int rc = launch_block_graphs(R, busy, k);
         if (rc) return rc;
     } else {
         Ctx c{e, Issue{R.s}, nk, R.timed, R.variant};
-        RCK(enqueue_block(c, k, R.F));
+        RCK(enqueue_block(c, busy, k, R.F));
     }
     RCK(hipMemcpyAsync(e->host[buf], e->st, state_bytes(e->N) + kAbortBytes, hipMemcpyDeviceToHost, R.s));
     RCK(hipEventRecord(e->ev[buf], R.s));
