@@ -139,7 +139,7 @@ struct stag_engine {
         hipStream_t s = nullptr;
         hipEvent_t done = nullptr;
     };
-    std::vector<Branch> gstreams;   // streams of the second and further groups
+    std::vector<Branch> gstreams;   // one per group of a block of several
     hipEvent_t gfork = nullptr;
     stag::HopTune tune_lo, tune_64;
 };

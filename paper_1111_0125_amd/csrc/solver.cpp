@@ -718,33 +718,43 @@ static int get_graph(EngineRun& R, int g0, int nk, int K, hipGraphExec_t* out) {
     return STAG_OK;
 }
 
-// One block as graphs: the first group's on the run's stream, each further
-// group's on a stream of the engine that starts after the run's stream and is
-// waited for by it, so the groups overlap on the device.
+// One block as graphs: a single group's on the run's stream; several groups'
+// each on a stream of the engine that starts after the run's stream and is
+// waited for by it, so the groups overlap on the device. The engine's streams
+// are created together, which gives them different hardware queues; the
+// run's stream may share one with any of them (5 RHS on 16^3 x 32, the first
+// group on the run's stream: 42 or 56 ms per solve, depending on what else had
+// created streams before).
 static int launch_block_graphs(EngineRun& R, int busy, int K) {
     stag_engine* e = R.e;
     const std::vector<Group> groups = slot_groups(e, busy);
     const int n = (int)groups.size();
-    if (n > 1) {
-        while ((int)e->gstreams.size() < n - 1) {
+    if (n > 1 && (int)e->gstreams.size() < n) {
+        if (!e->gfork) RCK(hipEventCreateWithFlags(&e->gfork, hipEventDisableTiming));
+        const size_t want = std::max((size_t)n, slot_groups(e, e->N).size());
+        while (e->gstreams.size() < want) {
             stag_engine::Branch br;
             RCK(hipStreamCreateWithFlags(&br.s, hipStreamNonBlocking));
             e->gstreams.push_back(br);
             RCK(hipEventCreateWithFlags(&e->gstreams.back().done, hipEventDisableTiming));
         }
-        if (!e->gfork) RCK(hipEventCreateWithFlags(&e->gfork, hipEventDisableTiming));
-        RCK(hipEventRecord(e->gfork, R.s));
     }
-    for (int i = n - 1; i >= 0; --i) {
+    if (n > 1) RCK(hipEventRecord(e->gfork, R.s));
+    for (int i = 0; i < n; ++i) {
         hipGraphExec_t exec = nullptr;
         int rc = get_graph(R, groups[i].g0, groups[i].n, K, &exec);
         if (rc) return rc;
-        const hipStream_t s = i == 0 ? R.s : e->gstreams[i - 1].s;
-        if (i > 0) RCK(hipStreamWaitEvent(s, e->gfork, 0));
-        RCK(hipGraphLaunch(exec, s));
-        if (i > 0) RCK(hipEventRecord(e->gstreams[i - 1].done, s));
+        if (n == 1) {
+            RCK(hipGraphLaunch(exec, R.s));
+            continue;
+        }
+        stag_engine::Branch& br = e->gstreams[i];
+        RCK(hipStreamWaitEvent(br.s, e->gfork, 0));
+        RCK(hipGraphLaunch(exec, br.s));
+        RCK(hipEventRecord(br.done, br.s));
     }
-    for (int i = 1; i < n; ++i) RCK(hipStreamWaitEvent(R.s, e->gstreams[i - 1].done, 0));
+    if (n > 1)
+        for (int i = 0; i < n; ++i) RCK(hipStreamWaitEvent(R.s, e->gstreams[i].done, 0));
     return STAG_OK;
 }
 
