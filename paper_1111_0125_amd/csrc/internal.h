@@ -61,6 +61,10 @@ struct stag_ctx {
     int cus = 0;                   // compute units
     void* scratch = nullptr;       // this device's copy of the scratch array (scratch.hip)
     hipMemPool_t pool = nullptr;   // stream-ordered temporaries; keeps freed memory for reuse
+    // blocks given back by gauges and fields, oldest first (kept_alloc)
+    std::vector<std::pair<void*, size_t>> kept;
+    size_t kept_bytes = 0;
+    std::mutex kept_mu;
     size_t budget = 0;
     std::atomic<size_t> used{0};
     std::mutex mu;                 // guards the object lists and the workspace pool
@@ -214,6 +218,9 @@ constexpr size_t kScratchBytes = (size_t)48 << 20;
 hipError_t scratch_init(int device, void** out);
 int dev_alloc(stag_ctx* ctx, size_t bytes, void** p);
 void dev_free(stag_ctx* ctx, void* p, size_t bytes);
+int kept_alloc(stag_ctx* ctx, size_t bytes, void** p);
+void kept_free(stag_ctx* ctx, void* p, size_t bytes);
+void kept_release(stag_ctx* ctx, size_t most);
 
 struct DeviceGuard {
     int prev = -1;

@@ -116,10 +116,18 @@ hipError_t launch_finalize(int N, const Reduce& R, unsigned run_mask, const Issu
 
 // Layout conversion kernels (canonical complex128 <-> internal storage).
 // r12: 12-parameter layout.
+// fp64 and / or fp32 copies of both output parities in one pass over the
+// canonical links (null: copy not stored): the one-hop pairs of U or the fat
+// links, or (three) the three-hop pairs of the long links. bad_dev (r12, may be
+// null): set to 1 when a link is not SU(3) within tol.
+hipError_t launch_gauge_scatter(const void* W_dev, bool three, int npairs, void* const G64[2],
+                                void* const G32[2], const Geom& g, bool r12, double tol, int* bad_dev,
+                                hipStream_t stream);
+// fp16 + scale copy of one output parity.
 // Ulong_dev: long links of the improved operator (U_dev then holds the fat
 // links), or null; never together with r12.
-hipError_t launch_gauge_pack(int prec, const void* U_dev, const void* Ulong_dev, void* G,
-                             float* gscale, const Geom& g, int p_out, bool r12, hipStream_t stream);
+hipError_t launch_gauge_pack16(const void* U_dev, const void* Ulong_dev, void* G, float* gscale,
+                               const Geom& g, int p_out, bool r12, hipStream_t stream);
 // Sets *bad_dev = 1 when a link is not SU(3) within tol (bad_dev zeroed by the caller).
 hipError_t launch_su3_check(const void* U_dev, uint64_t nlinks, double tol, int* bad_dev,
                             hipStream_t stream);

@@ -113,6 +113,9 @@ int engine_create(stag_ctx* ctx, const stag_gauge* g, int prec, int N, bool serv
     for (auto& r : reqs) {
         if (hipMalloc(r.p, r.bytes) != hipSuccess) {
             (void)hipGetLastError();
+            kept_release(ctx, 0);
+            if (hipMalloc(r.p, r.bytes) == hipSuccess) continue;
+            (void)hipGetLastError();
             engine_destroy(e);
             return set_error(ctx, STAG_ENOMEM, "solver workspace: hipMalloc(%zu) failed", r.bytes);
         }
