@@ -713,6 +713,28 @@ int stag_dslash(stag_ctx* ctx, const stag_gauge* g, const stag_field* in, stag_f
     return STAG_OK;
 }
 
+// Lattices that one workgroup per right-hand side covers: A in one launch, no
+// intermediate in memory (the same bits).
+static bool tiny_A(const stag_gauge* g) { return g->npairs == 4 && g->g.Vh <= (uint32_t)kTinySites; }
+
+static int apply_A_tiny(stag_ctx* ctx, const stag_gauge* g, const double* mass, const stag_field* in,
+                        stag_field* out, hipStream_t s) {
+    TinyApplyArgs a{};
+    for (int q = 0; q < 2; ++q) {
+        a.G[q] = g->G[in->prec][q];
+        a.gscale[q] = in->prec == P16S ? g->gscale[q] : nullptr;
+    }
+    a.r12 = g->r12;
+    a.g = g->g;
+    a.in = in->data;
+    a.out = out->data;
+    a.in_rs = in->rs;
+    a.out_rs = out->rs;
+    for (int r = 0; r < in->nrhs; ++r) a.m2[r] = mass[r] * mass[r];
+    HIPCK(ctx, launch_tiny_apply(in->prec, in->nrhs, a, s));
+    return STAG_OK;
+}
+
 // The two hop stages of A for every right-hand side of `in`, with the odd
 // intermediate D_oe in at t (in->nrhs right-hand sides of in->rs bytes).
 static int apply_A_stages(stag_ctx* ctx, const stag_gauge* g, const double* mass,
@@ -755,6 +777,7 @@ int stag_apply_A(stag_ctx* ctx, const stag_gauge* g, const double* mass, const s
     if (rc) return rc;
     DeviceGuard dg(ctx->device);
     hipStream_t s = pick_stream(ctx, stream);
+    if (tiny_A(g)) return apply_A_tiny(ctx, g, mass, in, out, s);
     void* t = nullptr;
     HIPCK(ctx, hipMallocFromPoolAsync(&t, in->rs * in->nrhs, ctx->pool, s));
     rc = apply_A_stages(ctx, g, mass, in, out, t, s);
@@ -775,6 +798,7 @@ int stag_apply_A_noalloc(stag_ctx* ctx, const stag_gauge* g, const double* mass,
                          need, kScratchBytes);
     if (!ctx->scratch) return set_error(ctx, STAG_EDEVICE, "stag_apply_A_noalloc: no scratch");
     DeviceGuard dg(ctx->device);
+    if (tiny_A(g)) return apply_A_tiny(ctx, g, mass, in, out, pick_stream(ctx, stream));
     // every hop-stage-1 output site is written before stage 2 reads it, so
     // nothing in the scratch needs clearing
     return apply_A_stages(ctx, g, mass, in, out, ctx->scratch, pick_stream(ctx, stream));

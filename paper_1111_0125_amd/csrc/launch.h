@@ -154,6 +154,21 @@ constexpr int kBlock = 256;  // threads per block of every kernel
 // One-workgroup solves of tiny lattices (tiny.hip): one workgroup of
 // kTinyBlock threads per right-hand side runs the whole solve.
 constexpr int kTinyBlock = 512;
+// Sites per pass of a hop stage: four lanes per site, one hop pair each.
+constexpr int kTinySites = kTinyBlock / 4;
+
+struct TinyApplyArgs {
+    const void* G[2];        // hop links by output parity
+    const float* gscale[2];  // P16S site scales
+    int r12;
+    Geom g;
+    const void* in;
+    void* out;
+    size_t in_rs, out_rs;
+    double m2[kMaxN];
+};
+
+hipError_t launch_tiny_apply(int prec, int nrhs, const TinyApplyArgs& a, hipStream_t stream);
 
 struct TinyArgs {
     const void* G[2];        // inner-precision hop links by output parity

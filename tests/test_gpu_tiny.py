@@ -127,3 +127,35 @@ def test_zero_rhs_breakdown_free_and_cap(stag, ctx):
     assert rc == stag.STAG_ENOCONV and st[0]["iters"] == 7
     rc, st, _ = solve(stag, ctx, L, U, b[:1], [0.05], 1e-12, inner="f32", max_iter=7)
     assert rc == stag.STAG_ENOCONV and st[0]["iters"] == 7
+
+
+@pytest.mark.parametrize("L", [(2, 2, 2, 2), (4, 2, 4, 6), (4, 4, 4, 4), (4, 4, 4, 6)])
+@pytest.mark.parametrize("prec,r12", [("f64", False), ("f64", True), ("f32", True), ("f16s", False),
+                                      ("f16s", True)])
+def test_apply_in_one_workgroup_equals_two_stages(stag, ctx, L, prec, r12):
+    """A of up to 128 sites per parity (the first three; 4^4 fills the
+    workgroup) in one launch gives the bits of D applied twice and the m^2
+    update (fp16: the update rounds what D_eo returned unrounded, so there A is
+    compared through its own other path, blocks of one and of several)."""
+    U = links(L, "haar", 71)
+    g = ctx.gauge(L, U, precisions=(prec,), r12=r12)
+    n = 5
+    v = synth.gaussian_rhs(L, n, 72)
+    masses = [0.1 * (k + 1) for k in range(n)]
+    fi, fo = ctx.field(g, 0, prec, n).load(v), ctx.field(g, 0, prec, n)
+    stag.stag_apply_A(ctx, g, masses, fi, fo)
+    got = fo.store()
+    if prec != "f16s":
+        ft, fe = ctx.field(g, 1, prec, n), ctx.field(g, 0, prec, n)
+        stag.stag_dslash(ctx, g, fi, ft)
+        stag.stag_dslash(ctx, g, ft, fe)
+        x, h = fi.store(), fe.store()
+        T = np.float64 if prec == "f64" else np.float32
+        tol = 4 * np.finfo(T).eps  # one fused rounding against two
+        for k in range(n):
+            ref = masses[k] ** 2 * x[k] - h[k]
+            assert np.abs(got[k] - ref).max() <= tol * np.abs(ref).max()
+    f1, o1 = ctx.field(g, 0, prec, 1).load(v[3:4]), ctx.field(g, 0, prec, 1)
+    stag.stag_apply_A_noalloc(ctx, g, masses[3:4], f1, o1)
+    assert np.array_equal(o1.store()[0], got[3])
+    g.destroy()
