@@ -717,7 +717,7 @@ int stag_dslash(stag_ctx* ctx, const stag_gauge* g, const stag_field* in, stag_f
     // exactly nrhs: a spare slot without state would be processed too
     int done = 0;
     while (done < in->nrhs) {
-        const int Nk = fit_n(in->nrhs - done);
+        const int Nk = fit_n(in->nrhs - done, g->npairs);
         HopTune t = operator_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
         const char* ip = (const char*)in->data + (size_t)done * in->rs;
         char* op = (char*)out->data + (size_t)done * out->rs;
@@ -756,7 +756,7 @@ static int apply_A_stages(stag_ctx* ctx, const stag_gauge* g, const double* mass
                           const stag_field* in, stag_field* out, void* t, hipStream_t s) {
     int done = 0;
     while (done < in->nrhs) {
-        const int Nk = fit_n(in->nrhs - done);
+        const int Nk = fit_n(in->nrhs - done, g->npairs);
         double m2[kMaxN] = {0};
         for (int r = 0; r < Nk; ++r) m2[r] = mass[done + r] * mass[done + r];
         HopTune tu = operator_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);

@@ -705,7 +705,8 @@ static int get_graph(EngineRun& R, int g0, int nk, int K, hipGraphExec_t* out) {
     if (err == hipSuccess) {
         Issue is;
         is.gb = &gb;
-        Ctx c{e, is, g0 == 0 ? nk : 0, false, R.variant};
+        // a group that is not the whole engine takes its own size's launch shapes
+        Ctx c{e, is, nk == e->N ? nk : 0, false, R.variant};
         err = enqueue_slots(c, g0, nk, K, R.F);
     }
     hipGraphExec_t exec = nullptr;
