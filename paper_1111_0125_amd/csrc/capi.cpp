@@ -171,6 +171,16 @@ HopTune get_tune(stag_ctx* ctx, int prec, int N, uint32_t Vh, int npairs) {
     return t;
 }
 
+// Operator calls of 12 and more right-hand sides: whether blocks of 12 and 16
+// are taken whole (fit_n): with the improved operator, and in fp32 from 65536
+// sites per parity on (import, A, export of 12 RHS with full links, us, whole
+// against 8 + 4: 20 x 18 x 22 x 30 158 and 172; 20 x 18 x 18 x 22, 71280 sites,
+// 133 and 138; 14 x 16 x 16 x 20, 35840 sites, 99 and 77; the whole blocks of the
+// last two with the kernels before the links lay in tiles).
+static bool wide_blocks(const stag_gauge* g, int prec) {
+    return g->npairs == 8 || (prec == P32 && g->g.Vh >= 65536);
+}
+
 // Shape of the operator calls: fp32 with one right-hand side takes two lanes per
 // site on lattices of 131072 sites per parity or more unless a shape was set or
 // tuned (import, A, export, us: 24^3 x 48 75.8 against 78.9 with one lane, full
@@ -717,7 +727,7 @@ int stag_dslash(stag_ctx* ctx, const stag_gauge* g, const stag_field* in, stag_f
     // exactly nrhs: a spare slot without state would be processed too
     int done = 0;
     while (done < in->nrhs) {
-        const int Nk = fit_n(in->nrhs - done, g->npairs);
+        const int Nk = fit_n(in->nrhs - done, wide_blocks(g, in->prec));
         HopTune t = operator_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
         const char* ip = (const char*)in->data + (size_t)done * in->rs;
         char* op = (char*)out->data + (size_t)done * out->rs;
@@ -756,7 +766,7 @@ static int apply_A_stages(stag_ctx* ctx, const stag_gauge* g, const double* mass
                           const stag_field* in, stag_field* out, void* t, hipStream_t s) {
     int done = 0;
     while (done < in->nrhs) {
-        const int Nk = fit_n(in->nrhs - done, g->npairs);
+        const int Nk = fit_n(in->nrhs - done, wide_blocks(g, in->prec));
         double m2[kMaxN] = {0};
         for (int r = 0; r < Nk; ++r) m2[r] = mass[done + r] * mass[done + r];
         HopTune tu = operator_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);

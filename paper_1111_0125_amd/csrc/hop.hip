@@ -792,7 +792,12 @@ template <int P, int EPI>
 static hipError_t dispatch_epi(int S, int N, bool nt, const HopArgs& a, const Issue& is) {
     if (N == 1) {
         if constexpr (EPI != EPI_RESID && kUseHop1<P, HOP_NP>) {
-            if (nt && S == HOP_NP / 4 && !a.lazy_y && !a.gate && a.g.Vh < kHop32MaxSites &&
+            // fp32 solves of the improved operator: stage 2 and stage 1 with the
+            // deferred direction stay with k_hop (20 x 18 x 22 x 30 33.5 against
+            // 40.5 ms a solve, 24^3 x 48 79.9 against 82.6)
+            constexpr bool solve32 = P == P32 && EPI == EPI_XPAY_DOT;
+            if (nt && S == HOP_NP / 4 && !solve32 && !(P == P32 && a.lazy_r) && !a.lazy_y && !a.gate &&
+                a.g.Vh < kHop32MaxSites &&
                 !(EPI == EPI_XPAY && a.lazy_r) && !(a.fin.partials && (EPI != EPI_PLAIN || !a.lazy_r)))
                 return dispatch_hop1<P, EPI>(a, is);
         }

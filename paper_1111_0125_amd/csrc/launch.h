@@ -149,8 +149,8 @@ inline int pick_n(int n) {
 // side a block of 12 or 16 costs more than one of 8: import, A, export of 12 RHS on
 // 12^4 fp32 65 us against 85). The operator calls of the improved operator keep
 // blocks of 12 and 16 (12 RHS on 20 x 18 x 22 x 30 fp32: 226 us against 257 as 8 + 4).
-inline int fit_n(int n, int npairs = 4) {
-    if (npairs == 8 && n >= 12) return n >= 16 ? 16 : 12;
+inline int fit_n(int n, bool wide = false) {
+    if (wide && n >= 12) return n >= 16 ? 16 : 12;
     return n >= 8 ? 8 : n >= 4 ? 4 : n;
 }
 
