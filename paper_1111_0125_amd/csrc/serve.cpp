@@ -218,6 +218,8 @@ static int admit(Serve* S, Work& w) {
     }
     std::vector<int> taken;
     auto release = [&]() {
+        // the ticket fails: its host vectors may be gone once it is collected
+        (void)hipStreamSynchronize(bt->stream);
         for (int s : taken) bt->slot_ticket[s] = nullptr;
     };
     int k = 0;

@@ -34,7 +34,15 @@ static bool persist_capable(const stag_gauge* g) {
 }
 static size_t ex_bytes(int N) { return (size_t)N * 4 * kPersistBlocks * sizeof(unsigned long long); }
 
+// Wait until everything launched on the engine's own streams has ended, for the
+// host too: the stream that a block was joined to can be idle while the runtime
+// has yet to retire a group's last graph launch.
+static void engine_drain(stag_engine* e) {
+    for (auto& br : e->gstreams) (void)hipStreamSynchronize(br.s);
+}
+
 void engine_drop_graphs(stag_engine* e) {
+    engine_drain(e);
     for (auto& kv : e->graphs)
         if (kv.second) (void)hipGraphExecDestroy(kv.second);
     e->graphs.clear();
@@ -744,22 +752,32 @@ static int launch_block_graphs(EngineRun& R, int busy, int K) {
         }
     }
     if (n > 1) RCK(hipEventRecord(e->gfork, R.s));
-    for (int i = 0; i < n; ++i) {
+    auto launch = [&](int i) -> int {
         hipGraphExec_t exec = nullptr;
         int rc = get_graph(R, groups[i].g0, groups[i].n, K, &exec);
         if (rc) return rc;
         if (n == 1) {
             RCK(hipGraphLaunch(exec, R.s));
-            continue;
+            return STAG_OK;
         }
         stag_engine::Branch& br = e->gstreams[i];
         RCK(hipStreamWaitEvent(br.s, e->gfork, 0));
         RCK(hipGraphLaunch(exec, br.s));
         RCK(hipEventRecord(br.done, br.s));
-    }
-    if (n > 1)
-        for (int i = 0; i < n; ++i) RCK(hipStreamWaitEvent(R.s, e->gstreams[i].done, 0));
-    return STAG_OK;
+        return STAG_OK;
+    };
+    auto launch_all = [&]() -> int {
+        for (int i = 0; i < n; ++i) {
+            const int rc = launch(i);
+            if (rc) return rc;
+        }
+        if (n > 1)
+            for (int i = 0; i < n; ++i) RCK(hipStreamWaitEvent(R.s, e->gstreams[i].done, 0));
+        return STAG_OK;
+    };
+    const int rc = launch_all();
+    if (rc) engine_drain(e);  // groups launched before, that the run's stream may not wait for
+    return rc;
 }
 
 // ------------------------------------------------------------------ resident iterations
@@ -1025,9 +1043,23 @@ static bool finishes_within(const std::vector<RhsState>& a, const std::vector<Rh
     return true;
 }
 
+// Waits for its stream when it goes, unless `idle` says that it was waited for.
+struct WaitAtExit {
+    hipStream_t stream;
+    bool idle = false;
+    ~WaitAtExit() {
+        if (!idle) (void)hipStreamSynchronize(stream);
+    }
+};
+
 int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, size_t b_rs,
                  void* x_out, size_t x_rs, const stag_cg_params& p, stag_cg_stats* stats,
                  hipStream_t stream, bool escalating) {
+    // held while the resident kernel is in use (below), and until it has ended
+    std::unique_lock<std::mutex> resident(persist_mutex(e->ctx->device), std::defer_lock);
+    // a solve that fails leaves nothing running on the engine, which is lent to
+    // the next one
+    WaitAtExit wait{stream};
     const auto t0 = std::chrono::steady_clock::now();
     const int K = p.graph_k > 0 ? p.graph_k : default_graph_k(e->Vh);
     RCK(hipMemcpy2DAsync(e->b64, e->rs64, b64, b_rs, e->rs64, n, hipMemcpyDeviceToDevice, stream));
@@ -1035,14 +1067,15 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     if (tiny_solve_eligible(e, n, p)) {
         int rc = tiny_solve(e, n, mass, p, escalating, stream, fin);
         if (rc) return rc;
-        return engine_solve_finish(e, n, x_out, x_rs, stats, stream, fin, t0);
+        rc = engine_solve_finish(e, n, x_out, x_rs, stats, stream, fin, t0);
+        wait.idle = rc != STAG_EDEVICE;
+        return rc;
     }
     EngineRun R;
     run_init(R, e, stream, e->b64, e->rs64, K, p.use_graph != 0);
     R.variant = e->prec != P64 ? p.mixed_variant : MIXED_CARRY;
     // small lattices: the iterations in a resident kernel, unless another solve
     // of this process has one on the device (the results are the same bits)
-    std::unique_lock<std::mutex> resident(persist_mutex(e->ctx->device), std::defer_lock);
     if (p.small_lattice != 0 && R.use_graph && (R.persist = persist_lanes(e, n)) != 0 &&
         !resident.try_lock())
         R.persist = 0;
@@ -1106,7 +1139,9 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     }
     RCK(hipStreamSynchronize(stream));
     if (R.timed) timing_collect(e->ctx);
-    return engine_solve_finish(e, n, x_out, x_rs, stats, stream, fin, t0);
+    rc = engine_solve_finish(e, n, x_out, x_rs, stats, stream, fin, t0);
+    wait.idle = rc != STAG_EDEVICE;
+    return rc;
 }
 
 }  // namespace stag

@@ -1,0 +1,139 @@
+// Scenarios of the library's host code on the stand-in runtime: one per run,
+// named by the first argument; the exit status says whether it held.
+#include <chrono>
+#include <cstdio>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include <hip/hip_runtime.h>
+
+#include "../../include/stag.h"
+#include "hip_stub.h"
+
+using hipstub::ctl;
+
+static int failures = 0;
+#define CHECK(c)                                                    \
+    do {                                                            \
+        if (!(c)) {                                                 \
+            ++failures;                                             \
+            fprintf(stderr, "line %d: %s does not hold\n", __LINE__, #c); \
+        }                                                           \
+    } while (0)
+
+struct Lattice {
+    int L[4];
+    size_t vh() const { return (size_t)L[0] * L[1] * L[2] * L[3] / 2; }
+};
+
+static stag_gauge* make_gauge(stag_ctx* c, const Lattice& l, int mask) {
+    std::vector<double> U(l.vh() * 2 * 72, 0.0);
+    stag_gauge* g = nullptr;
+    CHECK(stag_gauge_create(c, l.L, U.data(), 0, mask, &g) == STAG_OK);
+    return g;
+}
+
+static stag_field* make_field(stag_ctx* c, stag_gauge* g, int prec, int n, int parity = 0) {
+    stag_field* f = nullptr;
+    CHECK(stag_field_create(c, g, parity, prec, n, &f) == STAG_OK);
+    return f;
+}
+
+struct Solve {
+    int prec = STAG_F32, n = 1, use_graph = 1, small = 1;
+    hipStream_t stream = nullptr;
+};
+
+static int solve(stag_ctx* c, stag_gauge* g, const Solve& s) {
+    stag_field *b = make_field(c, g, STAG_F64, s.n), *x = make_field(c, g, STAG_F64, s.n);
+    std::vector<double> mass(s.n, 0.1);
+    std::vector<stag_cg_stats> st(s.n);
+    stag_cg_params p;
+    stag_cg_params_default(&p);
+    p.inner_prec = s.prec;
+    p.use_graph = s.use_graph;
+    p.small_lattice = s.small;
+    const int rc = stag_cg_solve(c, g, mass.data(), b, x, &p, st.data(), s.stream);
+    if (rc == STAG_OK)
+        for (auto& t : st) CHECK(t.status == STAG_OK && t.true_rel_res == 0.0);
+    stag_field_destroy(b);
+    stag_field_destroy(x);
+    return rc;
+}
+
+static const Lattice k44{{4, 4, 4, 4}}, k66{{6, 6, 6, 6}}, k88{{8, 8, 8, 8}}, k16{{16, 16, 16, 16}};
+
+static void wait_ticket(stag_ctx* c, stag_ticket t) {
+    while (stag_solver_poll(c, t, nullptr, nullptr, nullptr) == STAG_PENDING)
+        std::this_thread::sleep_for(std::chrono::microseconds(200));
+}
+
+// Nothing is destroyed before the runtime has retired its work: solves of
+// every group pattern, a change of the launch shapes (which drops the graphs),
+// gauges and contexts destroyed right after, serving batches released.
+static void lifetime() {
+    for (int n : {1, 3, 5, 8, 11, 16}) {
+        stag_ctx* c = nullptr;
+        CHECK(stag_create(0, 0, &c) == STAG_OK);
+        stag_gauge* g = make_gauge(c, k88, STAG_MASK_F64 | STAG_MASK_F32);
+        hipStream_t own = nullptr;
+        (void)hipStreamCreateWithFlags(&own, 0);
+        stag_field *b = make_field(c, g, STAG_F64, n), *x = make_field(c, g, STAG_F64, n);
+        std::vector<double> mass(n, 0.1), v(k88.vh() * 6 * n, 1.0);
+        stag_cg_params p;
+        stag_cg_params_default(&p);
+        p.inner_prec = STAG_F32;
+        p.small_lattice = 0;
+        CHECK(stag_cg_solve(c, g, mass.data(), b, x, &p, nullptr, own) == STAG_OK);
+        stag_tune_cfg t;
+        CHECK(stag_tune_get(c, STAG_F32, n, (int64_t)k88.vh(), &t) == STAG_OK);
+        CHECK(stag_tune_set(c, STAG_F32, n, (int64_t)k88.vh(), &t) == STAG_OK);
+        CHECK(stag_cg_solve(c, g, mass.data(), b, x, &p, nullptr, own) == STAG_OK);
+        stag_gauge_destroy(g);
+        g = make_gauge(c, k88, STAG_MASK_F64 | STAG_MASK_F32);
+        stag_ticket id = 0;
+        CHECK(stag_solver_submit(c, g, 0.1, n, v.data(), 1e-8, STAG_F32, &id) == STAG_OK);
+        wait_ticket(c, id);
+        CHECK(stag_gauge_destroy(g) == STAG_OK);
+        stag_destroy(c);
+        (void)hipStreamSynchronize(own);
+        (void)hipStreamDestroy(own);
+    }
+}
+
+// A solve that ends with a launch error leaves nothing of its own running.
+static void launch_error() {
+    for (int at : {1, 2, 3, 4}) {
+        stag_ctx* c = nullptr;
+        CHECK(stag_create(0, 0, &c) == STAG_OK);
+        stag_gauge* g = make_gauge(c, k88, STAG_MASK_F64 | STAG_MASK_F32);
+        stag_field *b = make_field(c, g, STAG_F64, 8), *x = make_field(c, g, STAG_F64, 8);
+        std::vector<double> mass(8, 0.1);
+        stag_cg_params p;
+        stag_cg_params_default(&p);
+        p.inner_prec = STAG_F32;
+        p.small_lattice = 0;
+        ctl.fail_graph_launch = at;
+        CHECK(stag_cg_solve(c, g, mass.data(), b, x, &p, nullptr, nullptr) == STAG_EDEVICE);
+        CHECK(hipstub::in_flight() == 0);
+        ctl.fail_graph_launch = 0;
+        CHECK(stag_cg_solve(c, g, mass.data(), b, x, &p, nullptr, nullptr) == STAG_OK);
+        stag_destroy(c);
+    }
+}
+
+int main(int argc, char** argv) {
+    static const std::map<std::string, std::function<void()>> all = {
+        {"lifetime", lifetime},
+        {"launch_error", launch_error},
+    };
+    auto it = argc > 1 ? all.find(argv[1]) : all.end();
+    if (it == all.end()) return 2;
+    it->second();
+    fflush(nullptr);
+    _Exit(failures || hipstub::violations() ? 1 : 0);
+}
