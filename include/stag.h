@@ -259,8 +259,8 @@ typedef struct stag_cg_params {
                           parity (16^3 x 32; plain CG: 32768) as long as the
                           right-hand sides of the call fit on the device together,
                           take a group of resident workgroups per right-hand side,
-                          with the bits of the kernel-per-stage solver (with
-                          use_graph only; a second such solve in the process at the
+                          with the bits of the kernel-per-stage solver (above
+                          648 sites with use_graph only; a second such solve in the process at the
                           same time on the same device takes the kernel-per-stage
                           solver). Eq.5 gauges only.
                           0: always the kernel-per-stage solver */

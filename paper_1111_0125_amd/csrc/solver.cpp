@@ -936,11 +936,15 @@ void fill_stats(const RhsState& s, double secs, int inner_prec, stag_cg_stats* o
 // 7.7; fp16 8.1 / 8.1 and 7.3 / 8.6; 2^4 fp32 5.3 / 5.8 and 10.5 / 20).
 constexpr uint32_t kTinySitesOnePass = 128;
 constexpr uint32_t kTinySitesGroups = 64;
+// Up to here (6^4) the resident groups serve solves without graphs too
+// (use_graph = 0): stages launched one by one are the slowest way of all on such
+// lattices (6^4, 8 RHS, fp32: 51 ms in one workgroup each, over 104 by stages).
+constexpr uint32_t kNoGraphSites = 648;
 
 static bool tiny_solve_eligible(const stag_engine* e, int n, const stag_cg_params& p) {
     const bool variant_ok = e->prec == P64 || p.mixed_variant == MIXED_CARRY ||
                             p.mixed_variant == MIXED_RESTART;
-    const bool groups = e->Vh > kTinySitesGroups && p.use_graph != 0 && persist_lanes(e, n) != 0 &&
+    const bool groups = e->Vh > kTinySitesGroups && persist_lanes(e, n) != 0 &&
                         (e->prec == P64 || (e->prec == P32 && n == 1));
     const bool size_ok = e->Vh <= kTinySitesOnePass && !groups;
     return p.small_lattice != 0 && size_ok && e->gauge->npairs == 4 && !p.use_x0 && variant_ok &&
@@ -1076,8 +1080,8 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     R.variant = e->prec != P64 ? p.mixed_variant : MIXED_CARRY;
     // small lattices: the iterations in a resident kernel, unless another solve
     // of this process has one on the device (the results are the same bits)
-    if (p.small_lattice != 0 && R.use_graph && (R.persist = persist_lanes(e, n)) != 0 &&
-        !resident.try_lock())
+    if (p.small_lattice != 0 && !R.timed && (R.use_graph || e->Vh <= kNoGraphSites) &&
+        (R.persist = persist_lanes(e, n)) != 0 && !resident.try_lock())
         R.persist = 0;
     R.nrhs = n;
     std::vector<SlotInit> slots(n);

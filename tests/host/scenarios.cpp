@@ -126,10 +126,51 @@ static void launch_error() {
     }
 }
 
+// Which kernels a solve took.
+struct Path {
+    int persist, tiny;
+};
+static Path path_of(const Lattice& l, const Solve& s) {
+    stag_ctx* c = nullptr;
+    CHECK(stag_create(0, 0, &c) == STAG_OK);
+    stag_gauge* g = make_gauge(c, l, STAG_MASK_F64 | STAG_MASK_F32 | STAG_MASK_F16S);
+    const int p0 = ctl.persist, t0 = ctl.tiny;
+    CHECK(solve(c, g, s) == STAG_OK);
+    const Path r{ctl.persist - p0, ctl.tiny - t0};
+    stag_destroy(c);
+    return r;
+}
+
+// Lattices of up to 648 sites per parity are solved inside a kernel whether
+// graphs are asked for or not.
+static void small_without_graphs() {
+    for (const Lattice& l : {k44, k66})
+        for (int prec : {STAG_F64, STAG_F32, STAG_F16S})
+            for (int n : {1, 4, 16})
+                for (int graph : {0, 1}) {
+                    Solve s;
+                    s.prec = prec;
+                    s.n = n;
+                    s.use_graph = graph;
+                    const Path p = path_of(l, s);
+                    CHECK(p.persist + p.tiny > 0);
+                    s.use_graph = 1 - graph;
+                    const Path q = path_of(l, s);
+                    CHECK((p.persist > 0) == (q.persist > 0) && (p.tiny > 0) == (q.tiny > 0));
+                    s.small = 0;
+                    const Path r = path_of(l, s);
+                    CHECK(r.persist + r.tiny == 0);
+                }
+    Solve s;
+    s.use_graph = 0;
+    CHECK(path_of(k88, s).persist == 0);
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
         {"launch_error", launch_error},
+        {"small_without_graphs", small_without_graphs},
     };
     auto it = argc > 1 ? all.find(argv[1]) : all.end();
     if (it == all.end()) return 2;
