@@ -254,15 +254,15 @@ typedef struct stag_cg_params {
                           iterations itself (no kernel launch per stage). Up to 128
                           sites per parity (4^4) one workgroup per right-hand side
                           (CARRY / RESTART mixed variants and plain CG, without
-                          use_x0), except plain CG and single F32 solves from 65
-                          sites on; those, and lattices of up to 65536 sites per
-                          parity (16^3 x 32; plain CG: 32768) as long as the
-                          right-hand sides of the call fit on the device together,
-                          take a group of resident workgroups per right-hand side,
-                          with the bits of the kernel-per-stage solver (above
-                          648 sites with use_graph only; a second such solve in the process at the
-                          same time on the same device takes the kernel-per-stage
-                          solver). Eq.5 gauges only.
+                          use_x0), except plain CG from 65 sites on; that, and
+                          lattices of up to 65536 sites per parity (16^3 x 32;
+                          plain CG: 32768) as long as the right-hand sides of the
+                          call fit on the device together, take a group of resident
+                          workgroups per right-hand side, with the bits of the
+                          kernel-per-stage solver (above 648 sites with use_graph
+                          only; a second such solve in the process at the same time
+                          on the same device takes the kernel-per-stage solver).
+                          Eq.5 gauges only.
                           0: always the kernel-per-stage solver */
 } stag_cg_params;
 

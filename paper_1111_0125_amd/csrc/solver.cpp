@@ -928,12 +928,15 @@ void fill_stats(const RhsState& s, double secs, int inner_prec, stag_cg_stats* o
 
 // Lattices that one pass of four lanes per site covers (128 sites per parity,
 // 4^4) are solved by one workgroup per right-hand side (tiny.hip), whose
-// barriers stay inside a compute unit. From 65 sites on the resident groups of
-// workgroups (persist.hip) are faster for plain CG, whose products one
-// workgroup's four wavefront slots cannot hide, and for a single fp32 solve (4^4,
-// us per iteration with 1 / 8 RHS: fp64 13.0 / 13.1 in one workgroup, 7.5 / 8.6 in
-// groups; fp32 8.8 / 8.9 and 6.3 / 7.5, with 12-parameter links 7.5 / 7.5 and 6.1 /
-// 7.7; fp16 8.1 / 8.1 and 7.3 / 8.6; 2^4 fp32 5.3 / 5.8 and 10.5 / 20).
+// barriers stay inside a compute unit; plain CG from 65 sites on by the resident
+// groups of workgroups (persist.hip), because one workgroup's four wavefront
+// slots cannot hide its products (4^4, us per iteration with 1 / 8 RHS: fp64 13.0 /
+// 13.1 in one workgroup, 7.5 / 8.6 in groups; 2^4 5.3 / 5.8 and 10.5 / 20 in fp32).
+// The two add their sums in another order, so the line depends on the
+// lattice and the precision alone, never on how many right-hand sides a call
+// has or on what else is running: a single fp32 solve would be faster in groups
+// (6.3 us against 8.8, 12-parameter links 6.1 against 7.5), eight are not (7.7
+// against 7.5), and both have to give the same bits.
 constexpr uint32_t kTinySitesOnePass = 128;
 constexpr uint32_t kTinySitesGroups = 64;
 // Up to here (6^4) the resident groups serve solves without graphs too
@@ -941,11 +944,10 @@ constexpr uint32_t kTinySitesGroups = 64;
 // lattices (6^4, 8 RHS, fp32: 51 ms in one workgroup each, over 104 by stages).
 constexpr uint32_t kNoGraphSites = 648;
 
-static bool tiny_solve_eligible(const stag_engine* e, int n, const stag_cg_params& p) {
+static bool tiny_solve_eligible(const stag_engine* e, const stag_cg_params& p) {
     const bool variant_ok = e->prec == P64 || p.mixed_variant == MIXED_CARRY ||
                             p.mixed_variant == MIXED_RESTART;
-    const bool groups = e->Vh > kTinySitesGroups && persist_lanes(e, n) != 0 &&
-                        (e->prec == P64 || (e->prec == P32 && n == 1));
+    const bool groups = e->Vh > kTinySitesGroups && e->prec == P64;
     const bool size_ok = e->Vh <= kTinySitesOnePass && !groups;
     return p.small_lattice != 0 && size_ok && e->gauge->npairs == 4 && !p.use_x0 && variant_ok &&
            !e->ctx->timing.on;
@@ -1068,7 +1070,7 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     const int K = p.graph_k > 0 ? p.graph_k : default_graph_k(e->Vh);
     RCK(hipMemcpy2DAsync(e->b64, e->rs64, b64, b_rs, e->rs64, n, hipMemcpyDeviceToDevice, stream));
     std::vector<RhsState> fin(n);
-    if (tiny_solve_eligible(e, n, p)) {
+    if (tiny_solve_eligible(e, p)) {
         int rc = tiny_solve(e, n, mass, p, escalating, stream, fin);
         if (rc) return rc;
         rc = engine_solve_finish(e, n, x_out, x_rs, stats, stream, fin, t0);

@@ -166,10 +166,27 @@ static void small_without_graphs() {
     CHECK(path_of(k88, s).persist == 0);
 }
 
+// What solves a lattice of up to 128 sites per parity does not depend on how many
+// right-hand sides the call has (the two solvers add their sums in another order).
+static void small_same_for_blocks() {
+    for (const Lattice& l : {Lattice{{2, 2, 2, 2}}, Lattice{{4, 4, 4, 2}}, k44})
+        for (int prec : {STAG_F64, STAG_F32, STAG_F16S}) {
+            Solve s;
+            s.prec = prec;
+            const Path one = path_of(l, s);
+            for (int n : {2, 5, 16}) {
+                s.n = n;
+                const Path p = path_of(l, s);
+                CHECK((p.tiny > 0) == (one.tiny > 0) && (p.persist > 0) == (one.persist > 0));
+            }
+        }
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
         {"launch_error", launch_error},
+        {"small_same_for_blocks", small_same_for_blocks},
         {"small_without_graphs", small_without_graphs},
     };
     auto it = argc > 1 ? all.find(argv[1]) : all.end();

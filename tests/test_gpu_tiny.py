@@ -159,3 +159,21 @@ def test_apply_in_one_workgroup_equals_two_stages(stag, ctx, L, prec, r12):
     stag.stag_apply_A_noalloc(ctx, g, masses[3:4], f1, o1)
     assert np.array_equal(o1.store()[0], got[3])
     g.destroy()
+
+
+@pytest.mark.parametrize("inner,r12", [("f64", False), ("f64", True), ("f32", False), ("f32", True),
+                                       ("f16s", True)])
+@pytest.mark.parametrize("L", [(2, 2, 2, 2), (4, 4, 4, 4)])
+def test_bits_do_not_depend_on_the_batch_or_on_graphs(stag, ctx, L, inner, r12):
+    """A right-hand side of a batch, and one solved without graphs, has the bits
+    and iterations of its solve alone."""
+    U = links(L, "haar", 91)
+    masses = [0.2, 0.25, 0.3, 0.35]
+    b = synth.gaussian_rhs(L, 4, 92)
+    rc, st, x = solve(stag, ctx, L, U, b, masses, 1e-9, inner=inner, r12=r12)
+    rcg, stg, xg = solve(stag, ctx, L, U, b, masses, 1e-9, inner=inner, r12=r12, use_graph=False)
+    assert rc == 0 and rcg == 0 and np.array_equal(x, xg)
+    for k in range(4):
+        rc1, st1, x1 = solve(stag, ctx, L, U, b[k:k + 1], masses[k:k + 1], 1e-9, inner=inner, r12=r12)
+        assert rc1 == 0 and st1[0]["iters"] == st[k]["iters"]
+        assert np.array_equal(x1[0], x[k]), k
