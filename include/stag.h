@@ -101,7 +101,10 @@ int stag_version(void);
  * stag_create: bind a context to HIP device `device` (0-based) and create
  * its stream. `hbm_budget_bytes` caps the device memory the context may
  * hold (gauges, fields, solver workspaces); 0 means all currently free
- * memory. Errors: EINVAL (null out, bad device), EDEVICE.
+ * memory. The memory of destroyed gauges and fields is kept for the next
+ * ones of the same size, up to 4 GiB: it counts against the budget, and is
+ * given back before an object is refused, when an allocation fails and by
+ * stag_destroy. Errors: EINVAL (null out, bad device), EDEVICE.
  * stag_destroy: waits for the context's work, cancels pending serving
  * tickets, frees every object created from the context. NULL is a no-op.
  * stag_last_error: text of the last error on the context (or of the last
@@ -110,7 +113,8 @@ int stag_version(void);
 int stag_create(int device, size_t hbm_budget_bytes, stag_ctx** out);
 int stag_destroy(stag_ctx* ctx);
 const char* stag_last_error(const stag_ctx* ctx);
-/* Bytes of device memory currently held by the context. */
+/* Bytes of device memory currently held by the context, the memory kept from
+ * destroyed gauges and fields included. */
 int stag_memory_used(const stag_ctx* ctx, size_t* bytes);
 
 /* ---------------------------------------------------------------- gauge

@@ -31,25 +31,47 @@ int set_error(stag_ctx* ctx, int code, const char* fmt, ...) {
     return code;
 }
 
-int dev_alloc(stag_ctx* ctx, size_t bytes, void** p) {
-    *p = nullptr;
-    if (bytes == 0) return STAG_OK;
-    size_t prev = ctx->used.fetch_add(bytes);
-    if (ctx->budget && prev + bytes > ctx->budget) {
-        ctx->used.fetch_sub(bytes);
-        return set_error(ctx, STAG_ENOMEM, "HBM budget exceeded: %zu + %zu > %zu bytes", prev,
-                         bytes, ctx->budget);
+// Count `bytes` as used by a new object. The budget covers what the context's
+// objects use and the memory kept from destroyed ones together: kept blocks in
+// the way of the new object are given back, the longest unused first.
+int budget_take(stag_ctx* ctx, size_t bytes, const char* what) {
+    std::vector<void*> drop;
+    {
+        std::lock_guard<std::mutex> lk(ctx->kept_mu);
+        const size_t used = ctx->used.load();
+        if (ctx->budget && used + bytes > ctx->budget)
+            return set_error(ctx, STAG_ENOMEM, "%s: HBM budget exceeded: %zu + %zu > %zu bytes", what,
+                             used, bytes, ctx->budget);
+        ctx->used += bytes;
+        if (ctx->budget) kept_take_above(ctx, ctx->budget - used - bytes, drop);
     }
+    for (void* p : drop) (void)hipFree(p);
+    return STAG_OK;
+}
+
+// hipMalloc that gives back every kept block before it fails.
+hipError_t device_malloc(stag_ctx* ctx, void** p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        kept_release(ctx, 0);
+        kept_release(ctx);
         e = hipMalloc(p, bytes);
+        if (e != hipSuccess) {
+            *p = nullptr;
+            (void)hipGetLastError();
+        }
     }
+    return e;
+}
+
+int dev_alloc(stag_ctx* ctx, size_t bytes, void** p) {
+    *p = nullptr;
+    if (bytes == 0) return STAG_OK;
+    int rc = budget_take(ctx, bytes, "hipMalloc");
+    if (rc) return rc;
+    const hipError_t e = device_malloc(ctx, p, bytes);
     if (e != hipSuccess) {
         ctx->used.fetch_sub(bytes);
-        *p = nullptr;
-        (void)hipGetLastError();
         return set_error(ctx, STAG_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
     }
     return STAG_OK;
@@ -62,73 +84,66 @@ void dev_free(stag_ctx* ctx, void* p, size_t bytes) {
 }
 
 // Gauges and fields: what they give back is kept for the next object of the same
-// size, up to kKeepBytes per context, the longest unused going first: mapping
-// the copies of a configuration anew takes many times longer than filling
-// them (24^3 x 48, fp64 and fp32 12-parameter copies: 20 ms against 0.4). A block
-// is given back only when nothing on the device uses it (the callers wait),
-// so it may be handed out again at once, on any stream.
+// size, up to kKeepBytes per context and within its budget, the longest unused
+// going first: mapping the copies of a configuration anew takes many times
+// longer than filling them (24^3 x 48, fp64 and fp32 12-parameter copies: 20 ms
+// against 0.4). A block is given back only when nothing on the device uses it
+// (the callers wait), so it may be handed out again at once, on any stream.
 static constexpr size_t kKeepBytes = (size_t)4 << 30;
+
+// Take the longest unused blocks off the kept list until at most `most` bytes
+// stay (kept_mu held); the caller frees them.
+void kept_take_above(stag_ctx* ctx, size_t most, std::vector<void*>& drop) {
+    while (ctx->kept_bytes > most) {
+        drop.push_back(ctx->kept.front().first);
+        ctx->kept_bytes -= ctx->kept.front().second;
+        ctx->kept.erase(ctx->kept.begin());
+    }
+}
 
 int kept_alloc(stag_ctx* ctx, size_t bytes, void** p) {
     *p = nullptr;
     if (bytes == 0) return STAG_OK;
-    size_t prev = ctx->used.fetch_add(bytes);
-    if (ctx->budget && prev + bytes > ctx->budget) {
-        ctx->used.fetch_sub(bytes);
-        return set_error(ctx, STAG_ENOMEM, "HBM budget exceeded: %zu + %zu > %zu bytes", prev,
-                         bytes, ctx->budget);
-    }
     {
         std::lock_guard<std::mutex> lk(ctx->kept_mu);
         for (size_t i = ctx->kept.size(); i-- > 0;)
             if (ctx->kept[i].second == bytes) {
+                // from kept to used: what the context holds stays the same
                 *p = ctx->kept[i].first;
                 ctx->kept.erase(ctx->kept.begin() + i);
                 ctx->kept_bytes -= bytes;
+                ctx->used += bytes;
                 return STAG_OK;
             }
     }
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        kept_release(ctx, 0);
-        e = hipMalloc(p, bytes);
-    }
-    if (e != hipSuccess) {
-        ctx->used.fetch_sub(bytes);
-        *p = nullptr;
-        (void)hipGetLastError();
-        return set_error(ctx, STAG_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
-    }
-    return STAG_OK;
+    return dev_alloc(ctx, bytes, p);
 }
 
 void kept_free(stag_ctx* ctx, void* p, size_t bytes) {
     if (!p) return;
-    ctx->used.fetch_sub(bytes);
     if (bytes > kKeepBytes) {
-        (void)hipFree(p);
+        dev_free(ctx, p, bytes);
         return;
     }
-    kept_release(ctx, kKeepBytes - bytes);
-    std::lock_guard<std::mutex> lk(ctx->kept_mu);
-    ctx->kept.push_back({p, bytes});
-    ctx->kept_bytes += bytes;
+    std::vector<void*> drop;
+    {
+        std::lock_guard<std::mutex> lk(ctx->kept_mu);
+        kept_take_above(ctx, kKeepBytes - bytes, drop);
+        ctx->kept.push_back({p, bytes});
+        ctx->kept_bytes += bytes;
+        ctx->used -= bytes;
+    }
+    for (void* d : drop) (void)hipFree(d);
 }
 
-// Free kept blocks, the longest unused first, until at most `most` bytes stay.
-void kept_release(stag_ctx* ctx, size_t most) {
-    for (;;) {
-        void* p = nullptr;
-        {
-            std::lock_guard<std::mutex> lk(ctx->kept_mu);
-            if (ctx->kept_bytes <= most) return;
-            p = ctx->kept.front().first;
-            ctx->kept_bytes -= ctx->kept.front().second;
-            ctx->kept.erase(ctx->kept.begin());
-        }
-        (void)hipFree(p);
+// Free every kept block.
+void kept_release(stag_ctx* ctx) {
+    std::vector<void*> drop;
+    {
+        std::lock_guard<std::mutex> lk(ctx->kept_mu);
+        kept_take_above(ctx, 0, drop);
     }
+    for (void* p : drop) (void)hipFree(p);
 }
 
 Geom make_geom(const int L[4]) {
@@ -389,7 +404,7 @@ int stag_destroy(stag_ctx* ctx) {
         for (int q = 0; q < 2; ++q) (void)hipFree(g->gscale[q]);
         delete g;
     }
-    kept_release(ctx, 0);
+    kept_release(ctx);
     (void)hipStreamDestroy(ctx->stream);
     if (ctx->pool) (void)hipMemPoolDestroy(ctx->pool);
     delete ctx;
@@ -398,7 +413,8 @@ int stag_destroy(stag_ctx* ctx) {
 
 int stag_memory_used(const stag_ctx* ctx, size_t* bytes) {
     if (!ctx || !bytes) return STAG_EINVAL;
-    *bytes = ctx->used.load();
+    std::lock_guard<std::mutex> lk(ctx->kept_mu);
+    *bytes = ctx->used.load() + ctx->kept_bytes;
     return STAG_OK;
 }
 
@@ -456,14 +472,8 @@ int gauge_create(stag_ctx* ctx, const int L[4], const double* U, const double* U
     };
     if (!U_on_device) {
         const size_t sbytes = Ulong ? 2 * ubytes : ubytes;
-        hipError_t e = hipMalloc(&Ud, sbytes);
+        hipError_t e = device_malloc(ctx, &Ud, sbytes);
         if (e != hipSuccess) {
-            (void)hipGetLastError();
-            kept_release(ctx, 0);
-            e = hipMalloc(&Ud, sbytes);
-        }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
             cleanup();
             return set_error(ctx, STAG_ENOMEM, "stag_gauge_create: staging hipMalloc(%zu): %s",
                              sbytes, hipGetErrorString(e));

@@ -64,9 +64,9 @@ struct stag_ctx {
     // blocks given back by gauges and fields, oldest first (kept_alloc)
     std::vector<std::pair<void*, size_t>> kept;
     size_t kept_bytes = 0;
-    std::mutex kept_mu;
-    size_t budget = 0;
-    std::atomic<size_t> used{0};
+    mutable std::mutex kept_mu;
+    size_t budget = 0;             // covers used and kept_bytes together
+    std::atomic<size_t> used{0};   // by the context's objects
     std::mutex mu;                 // guards the object lists and the workspace pool
     std::string err;
     std::mutex err_mu;
@@ -220,7 +220,10 @@ int dev_alloc(stag_ctx* ctx, size_t bytes, void** p);
 void dev_free(stag_ctx* ctx, void* p, size_t bytes);
 int kept_alloc(stag_ctx* ctx, size_t bytes, void** p);
 void kept_free(stag_ctx* ctx, void* p, size_t bytes);
-void kept_release(stag_ctx* ctx, size_t most);
+void kept_take_above(stag_ctx* ctx, size_t most, std::vector<void*>& drop);
+void kept_release(stag_ctx* ctx);
+int budget_take(stag_ctx* ctx, size_t bytes, const char* what);
+hipError_t device_malloc(stag_ctx* ctx, void** p, size_t bytes);
 
 struct DeviceGuard {
     int prev = -1;

@@ -110,20 +110,14 @@ int engine_create(stag_ctx* ctx, const stag_gauge* g, int prec, int N, bool serv
     }
     size_t total = 0;
     for (auto& r : reqs) total += r.bytes;
-    size_t prev = ctx->used.fetch_add(total);
-    if (ctx->budget && prev + total > ctx->budget) {
-        ctx->used.fetch_sub(total);
+    const int taken = budget_take(ctx, total, "solver workspace");
+    if (taken) {
         delete e;
-        return set_error(ctx, STAG_ENOMEM, "solver workspace: HBM budget exceeded (%zu + %zu > %zu)",
-                         prev, total, ctx->budget);
+        return taken;
     }
     e->bytes = total;
     for (auto& r : reqs) {
-        if (hipMalloc(r.p, r.bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            kept_release(ctx, 0);
-            if (hipMalloc(r.p, r.bytes) == hipSuccess) continue;
-            (void)hipGetLastError();
+        if (device_malloc(ctx, r.p, r.bytes) != hipSuccess) {
             engine_destroy(e);
             return set_error(ctx, STAG_ENOMEM, "solver workspace: hipMalloc(%zu) failed", r.bytes);
         }

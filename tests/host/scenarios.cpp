@@ -182,10 +182,62 @@ static void small_same_for_blocks() {
         }
 }
 
+// The budget covers the memory kept from destroyed objects too: it is never
+// exceeded, kept memory is given back before an object is refused, and a block
+// used again comes back as a new one would (fields zero).
+static void budget() {
+    const size_t budget = 24u << 20;
+    stag_ctx* c = nullptr;
+    CHECK(stag_create(0, budget, &c) == STAG_OK);
+    auto held = [&] {
+        size_t b = 0;
+        CHECK(stag_memory_used(c, &b) == STAG_OK);
+        CHECK(b == ctl.malloc_held && b <= budget);
+        return b;
+    };
+    const Lattice sizes[] = {k88, {{8, 8, 8, 4}}, {{8, 8, 8, 12}}, {{8, 8, 4, 12}}, {{8, 8, 8, 16}}};
+    for (int k = 0; k < 25; ++k) {
+        const Lattice l = sizes[k % 5];
+        std::vector<double> U(l.vh() * 2 * 72, 0.0);
+        stag_gauge* g = nullptr;
+        CHECK(stag_gauge_create(c, l.L, U.data(), 1, STAG_MASK_F64 | STAG_MASK_F32, &g) == STAG_OK);
+        const int n = 1 + k % 3;
+        stag_field* f = make_field(c, g, STAG_F64, n);
+        std::vector<double> v(l.vh() * 6 * n, 1.0);
+        CHECK(stag_field_export(f, v.data(), 0, nullptr) == STAG_OK);
+        for (double x : v)
+            if (x != 0.0) {
+                CHECK(x == 0.0);
+                break;
+            }
+        v.assign(v.size(), 3.0);
+        CHECK(stag_field_import(f, v.data(), 0, nullptr) == STAG_OK);
+        Solve s;
+        s.n = 1;
+        CHECK(solve(c, g, s) == STAG_OK);
+        held();
+        stag_field_destroy(f);
+        CHECK(stag_gauge_destroy(g) == STAG_OK);
+        held();
+    }
+    CHECK(ctl.malloc_peak <= budget);
+    // an object larger than what is left is refused, one that fits once the kept
+    // memory is given back is not
+    stag_gauge *g = nullptr, *g2 = nullptr;
+    const Lattice big{{16, 16, 16, 8}}, most{{8, 8, 8, 26}};
+    std::vector<double> U(big.vh() * 2 * 72, 0.0);
+    CHECK(stag_gauge_create(c, big.L, U.data(), 1, STAG_MASK_F64, &g) == STAG_ENOMEM);
+    CHECK(stag_gauge_create(c, most.L, U.data(), 1, STAG_MASK_F64 | STAG_MASK_F32, &g2) == STAG_OK);
+    CHECK(held() > budget * 9 / 10);
+    stag_destroy(c);
+    CHECK(ctl.malloc_held == 0);
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
         {"launch_error", launch_error},
+        {"budget", budget},
         {"small_same_for_blocks", small_same_for_blocks},
         {"small_without_graphs", small_without_graphs},
     };
