@@ -136,6 +136,24 @@ void kept_free(stag_ctx* ctx, void* p, size_t bytes) {
     for (void* d : drop) (void)hipFree(d);
 }
 
+// Whether the device is known to be idle (a synchronisation can fail without
+// having waited, for instance while another thread captures a stream).
+static bool device_idle() {
+    if (hipDeviceSynchronize() == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// A destroyed object's block: kept for reuse only from an idle device, else
+// left to hipFree, which waits by itself.
+static void give_back(stag_ctx* ctx, void* p, size_t bytes, bool idle) {
+    if (idle) {
+        kept_free(ctx, p, bytes);
+    } else {
+        dev_free(ctx, p, bytes);
+    }
+}
+
 // Free every kept block.
 void kept_release(stag_ctx* ctx) {
     std::vector<void*> drop;
@@ -587,12 +605,12 @@ int stag_gauge_destroy(stag_gauge* g) {
     }
     for (auto* e : drop) engine_destroy(e);
     const size_t Vh = g->g.Vh;
-    (void)hipDeviceSynchronize();  // work on any stream may still read the links
+    const bool idle = device_idle();  // work on any stream may still read the links
     for (int p = 0; p < 3; ++p)
         for (int q = 0; q < 2; ++q)
-            if (g->G[p][q]) kept_free(ctx, g->G[p][q], link_bytes(p, Vh, g->r12, g->npairs));
+            if (g->G[p][q]) give_back(ctx, g->G[p][q], link_bytes(p, Vh, g->r12, g->npairs), idle);
     for (int q = 0; q < 2; ++q)
-        if (g->gscale[q]) kept_free(ctx, g->gscale[q], Vh * 4);
+        if (g->gscale[q]) give_back(ctx, g->gscale[q], Vh * 4, idle);
     delete g;
     return STAG_OK;
 }
@@ -658,8 +676,8 @@ int stag_field_destroy(stag_field* f) {
                 break;
             }
     }
-    (void)hipDeviceSynchronize();  // work on any stream may still use the field
-    kept_free(ctx, f->data, f->rs * f->nrhs);
+    // work on any stream may still use the field
+    give_back(ctx, f->data, f->rs * f->nrhs, device_idle());
     delete f;
     return STAG_OK;
 }

@@ -233,11 +233,41 @@ static void budget() {
     CHECK(ctl.malloc_held == 0);
 }
 
+// A device synchronisation that fails has not waited: what is destroyed then is
+// not handed out again while kernels may still use it.
+static void failed_sync() {
+    stag_ctx* c = nullptr;
+    CHECK(stag_create(0, 0, &c) == STAG_OK);
+    hipStream_t own = nullptr;
+    (void)hipStreamCreateWithFlags(&own, 0);
+    stag_gauge* g = make_gauge(c, k44, STAG_MASK_F64);
+    stag_field *a = make_field(c, g, STAG_F64, 1), *b = make_field(c, g, STAG_F64, 1);
+    const double m = 0.1;
+    ctl.kernel_ms = 100;
+    for (int k = 0; k < 2; ++k) {
+        CHECK(stag_apply_A(c, g, &m, a, b, own) == STAG_OK);
+        ctl.fail_device_sync = 1;
+        if (k == 0) {
+            stag_field_destroy(b);
+            b = make_field(c, g, STAG_F64, 1);
+        } else {
+            CHECK(stag_gauge_destroy(g) == STAG_OK);
+            g = make_gauge(c, k44, STAG_MASK_F64);
+        }
+        CHECK(hipstub::in_flight() == 0);
+        ctl.fail_device_sync = 0;
+    }
+    ctl.kernel_ms = 0;
+    stag_destroy(c);
+    CHECK(ctl.malloc_held == 0);
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
         {"launch_error", launch_error},
         {"budget", budget},
+        {"failed_sync", failed_sync},
         {"small_same_for_blocks", small_same_for_blocks},
         {"small_without_graphs", small_without_graphs},
     };
