@@ -64,6 +64,17 @@ hipError_t device_malloc(stag_ctx* ctx, void** p, size_t bytes) {
     return e;
 }
 
+// The same for a stream-ordered temporary of the context's pool.
+static hipError_t pool_malloc(stag_ctx* ctx, void** p, size_t bytes, hipStream_t s) {
+    hipError_t e = hipMallocFromPoolAsync(p, bytes, ctx->pool, s);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        kept_release(ctx);
+        e = hipMallocFromPoolAsync(p, bytes, ctx->pool, s);
+    }
+    return e;
+}
+
 int dev_alloc(stag_ctx* ctx, size_t bytes, void** p) {
     *p = nullptr;
     if (bytes == 0) return STAG_OK;
@@ -525,7 +536,7 @@ int gauge_create(stag_ctx* ctx, const int L[4], const double* U, const double* U
         constexpr double tol = 1e-10;
         const bool pass = g->G[P64][0] || g->G[P32][0];
         if (r12) {
-            e = hipMallocFromPoolAsync((void**)&bad, sizeof(int), ctx->pool, s);
+            e = pool_malloc(ctx, (void**)&bad, sizeof(int), s);
             if (e == hipSuccess) e = hipMemsetAsync(bad, 0, sizeof(int), s);
             if (e == hipSuccess && !pass) e = launch_su3_check(Usrc, (uint64_t)V * 4, tol, bad, s);
         }
@@ -693,7 +704,7 @@ int stag_field_import(stag_field* f, const double* src, int src_on_device, void*
     const void* dsrc = src;
     void* tmp = nullptr;
     if (!src_on_device) {
-        HIPCK(ctx, hipMallocFromPoolAsync(&tmp, bytes, ctx->pool, s));
+        HIPCK(ctx, pool_malloc(ctx, &tmp, bytes, s));
         HIPCK(ctx, hipMemcpyAsync(tmp, src, bytes, hipMemcpyHostToDevice, s));
         dsrc = tmp;
     }
@@ -716,7 +727,7 @@ int stag_field_export(const stag_field* f, double* dst, int dst_on_device, void*
     void* ddst = dst;
     void* tmp = nullptr;
     if (!dst_on_device) {
-        HIPCK(ctx, hipMallocFromPoolAsync(&tmp, bytes, ctx->pool, s));
+        HIPCK(ctx, pool_malloc(ctx, &tmp, bytes, s));
         ddst = tmp;
     }
     HIPCK(ctx, launch_export(f->prec, f->data, f->rs, ddst, (uint32_t)Vh, f->nrhs, s));
@@ -832,7 +843,7 @@ int stag_apply_A(stag_ctx* ctx, const stag_gauge* g, const double* mass, const s
     hipStream_t s = pick_stream(ctx, stream);
     if (tiny_A(g)) return apply_A_tiny(ctx, g, mass, in, out, s);
     void* t = nullptr;
-    HIPCK(ctx, hipMallocFromPoolAsync(&t, in->rs * in->nrhs, ctx->pool, s));
+    HIPCK(ctx, pool_malloc(ctx, &t, in->rs * in->nrhs, s));
     rc = apply_A_stages(ctx, g, mass, in, out, t, s);
     HIPCK(ctx, hipFreeAsync(t, s));
     return rc;

@@ -262,12 +262,36 @@ static void failed_sync() {
     CHECK(ctl.malloc_held == 0);
 }
 
+// Temporaries of the operator calls and host copies get the memory kept from
+// destroyed objects when the device has no other left.
+static void temporaries() {
+    stag_ctx* c = nullptr;
+    CHECK(stag_create(0, 0, &c) == STAG_OK);
+    stag_gauge* g = make_gauge(c, k88, STAG_MASK_F64);
+    stag_field *a = make_field(c, g, STAG_F64, 1), *b = make_field(c, g, STAG_F64, 1);
+    std::vector<double> v(k88.vh() * 6, 1.0);
+    const double m = 0.1;
+    for (int call = 0; call < 3; ++call) {
+        // kept memory: a gauge and its fields; then only a few KB more
+        stag_gauge* h = make_gauge(c, k66, STAG_MASK_F64);
+        CHECK(stag_gauge_destroy(h) == STAG_OK);
+        ctl.memory_limit = ctl.held + 4096;
+        if (call == 0) CHECK(stag_field_import(a, v.data(), 0, nullptr) == STAG_OK);
+        if (call == 1) CHECK(stag_field_export(a, v.data(), 0, nullptr) == STAG_OK);
+        if (call == 2) CHECK(stag_apply_A(c, g, &m, a, b, nullptr) == STAG_OK);
+        (void)hipDeviceSynchronize();
+        ctl.memory_limit = 0;
+    }
+    stag_destroy(c);
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
         {"launch_error", launch_error},
         {"budget", budget},
         {"failed_sync", failed_sync},
+        {"temporaries", temporaries},
         {"small_same_for_blocks", small_same_for_blocks},
         {"small_without_graphs", small_without_graphs},
     };
