@@ -265,7 +265,9 @@ typedef struct stag_cg_params {
                           workgroups per right-hand side, with the bits of the
                           kernel-per-stage solver (above 648 sites with use_graph
                           only; a second such solve in the process at the same time
-                          on the same device takes the kernel-per-stage solver).
+                          on the same device takes the kernel-per-stage solver,
+                          and so does every solve of a context after the waits
+                          inside such a kernel ran out once: stag_resident_wait).
                           Eq.5 gauges only.
                           0: always the kernel-per-stage solver */
 } stag_cg_params;
@@ -311,6 +313,18 @@ int stag_cg_solve(stag_ctx* ctx, const stag_gauge* gauge, const double* mass,
                   const stag_field* b, stag_field* x, const stag_cg_params* params,
                   stag_cg_stats* stats, void* stream);
 
+/* Resident kernels of small lattices (small_lattice above): their workgroups
+ * wait for each other inside the kernel, which needs all of them on the
+ * device. A wait that runs out (2 s; another process on the device can hold
+ * compute units) ends the kernel; the solve starts over with a kernel per
+ * stage, and so does every later one of the context.
+ * stag_resident_wait: sets the longest such wait in seconds (< 0: every wait
+ *   runs out at once) and lets the context use these kernels again. EINVAL.
+ * stag_resident_counts: solves that started in a resident kernel, and those of
+ *   them whose waits ran out. EINVAL.
+ */
+int stag_resident_wait(stag_ctx* ctx, double seconds);
+int stag_resident_counts(const stag_ctx* ctx, int64_t* solves, int64_t* gave_up);
 
 /* ---------------------------------------------------------------- serving
  * Continuous batching of solve requests (each a CG solve as in

@@ -136,6 +136,9 @@ def _load():
         "stag_solver_poll": ([vp, ctypes.c_int64, vp, ctypes.POINTER(CgStats),
                               ctypes.POINTER(dp)], ip),
         "stag_solver_config": ([vp, ip, ip, ip], ip),
+        "stag_resident_wait": ([vp, dp], ip),
+        "stag_resident_counts": ([vp, ctypes.POINTER(ctypes.c_int64),
+                                  ctypes.POINTER(ctypes.c_int64)], ip),
         "stag_timing_enable": ([vp, ip], ip),
         "stag_time_kernels": ([vp, vp, ip, ip, ip, ctypes.POINTER(dp)], ip),
         "stag_timing_read": ([vp, ip, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(dp)], ip),
@@ -350,6 +353,18 @@ def stag_cg_solve(ctx: Context, gauge: Gauge, mass, b: Field, x: Field, params: 
     if rc in (STAG_EINVAL, STAG_ENOMEM, STAG_EDEVICE):
         raise StagError(rc, ctx.last_error())
     return rc, [s.as_dict() for s in stats]
+
+
+def stag_resident_wait(ctx: Context, seconds: float):
+    """Longest wait inside a resident kernel (< 0: waits run out at once)."""
+    return ctx.check(lib.stag_resident_wait(ctx.h, float(seconds)))
+
+
+def stag_resident_counts(ctx: Context):
+    """(solves that started in a resident kernel, those whose waits ran out)."""
+    a, b = ctypes.c_int64(), ctypes.c_int64()
+    ctx.check(lib.stag_resident_counts(ctx.h, ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
 
 
 def stag_tune(ctx: Context, gauge: Gauge, prec="f32", nrhs=1):

@@ -77,6 +77,13 @@ struct stag_ctx {
     std::mutex tune_mu;
     std::atomic<int> tune_loaded{0};    // stag_tune calls answered from STAG_TUNE_CACHE
     std::atomic<int> tune_measured{0};  // stag_tune calls that timed the shapes
+    // Resident kernel of small lattices: solves that took it, those whose wait ran
+    // out (after one the context stays with a kernel per stage), and the longest
+    // wait in ticks of 10 ns (2 s: workgroups that are not resident yet wait for
+    // other streams' kernels to end, nothing else); below 0: no wait at all.
+    std::atomic<int64_t> resident_solves{0}, resident_gave_up{0};
+    std::atomic<int> resident_off{0};
+    std::atomic<long long> resident_wait{200000000};
     stag::Serve* serve = nullptr;
     stag::Timing timing;
 };

@@ -221,7 +221,7 @@ struct PersistArgs {
     int nrhs, blocks, one_xcd;
     int max_iters;              // iterations per launch
     uint32_t tag;               // even; tag + 1 .. tag + 2 max_iters + 1 are used and were not before
-    long long limit;            // longest wait, ticks of 10 ns
+    long long limit;            // longest wait, ticks of 10 ns; below 0: give up at once
 };
 
 hipError_t launch_persist(int prec, int S, bool r12, const PersistArgs& a, hipStream_t stream);

@@ -32,7 +32,7 @@
 //
 // Every wait ends: it is bounded in time, and a block whose wait runs out
 // raises the abort word and leaves; the host then solves with a kernel per
-// stage.
+// stage, and stays with that in the context.
 #include <type_traits>
 
 #include "kern.h"
@@ -303,7 +303,8 @@ __global__ __launch_bounds__(kBlock, 1) void k_persist(PersistArgs a) {
     __syncthreads();
     if (wave == 0) {
         double sum = 0.0;
-        if (!exchange<S>(ex, a.blocks, b, a.tag + 1, 0.0, a.limit, sum) && lane == 0) out = 1;
+        const bool ok = a.limit >= 0 && exchange<S>(ex, a.blocks, b, a.tag + 1, 0.0, a.limit, sum);
+        if (!ok && lane == 0) out = 1;
     }
     __syncthreads();
 

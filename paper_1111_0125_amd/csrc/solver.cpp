@@ -778,13 +778,10 @@ static int launch_block_graphs(EngineRun& R, int busy, int K) {
 
 // Iterations per launch of the resident kernel: a fix-up comes due every few
 // tens of iterations in mixed CG, so this only bounds how long one launch
-// keeps the device to itself (about 10 us an iteration).
+// keeps its compute units to itself (about 10 us an iteration).
 constexpr int kPersistIters = 1024;
 // Rounds (one launch and its fix-up) between polls.
 constexpr int kPersistRounds = 3;
-// Longest wait inside the resident kernel, ticks of 10 ns: blocks that are not
-// resident yet wait for other streams' kernels to end, nothing else.
-constexpr long long kPersistLimit = 200000000;  // 2 s
 
 // One resident kernel at a time per device and process: two of them, each
 // holding part of the compute units, would wait for each other.
@@ -803,7 +800,7 @@ static std::mutex& persist_mutex(int device) {
 // the kernel per stage is still slower (16^3 x 32, us per iteration: fp32 22.5
 // against 14.1, full links 26.1 against 21.5, fp16 19.5 against 16.8).
 static int persist_lanes(const stag_engine* e, int n) {
-    if (!e->ex) return 0;
+    if (!e->ex || e->ctx->resident_off) return 0;
     const bool wide = e->prec == P64 && !e->gauge->r12;
     const int order[3] = {wide ? 4 : 2, wide ? 2 : 1, 0};
     for (int k = 0; order[k]; ++k) {
@@ -840,7 +837,7 @@ static int enqueue_persist_rounds(EngineRun& R, int nk) {
     a.blocks = (int)hop_blocks(e->Vh, R.persist);
     a.one_xcd = a.blocks * ((R.nrhs + 7) / 8) <= 32;
     a.max_iters = kPersistIters;
-    a.limit = kPersistLimit;
+    a.limit = e->ctx->resident_wait;
     Ctx c{e, Issue{R.s}, nk, false, R.variant};
     for (int k = 0; k < kPersistRounds; ++k) {
         if (e->tag < 2 || e->tag > (1u << 30)) {
@@ -1077,8 +1074,10 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     // small lattices: the iterations in a resident kernel, unless another solve
     // of this process has one on the device (the results are the same bits)
     if (p.small_lattice != 0 && !R.timed && (R.use_graph || e->Vh <= kNoGraphSites) &&
-        (R.persist = persist_lanes(e, n)) != 0 && !resident.try_lock())
+        (R.persist = persist_lanes(e, n)) != 0 &&
+        !resident.try_lock())
         R.persist = 0;
+    if (R.persist) e->ctx->resident_solves += 1;
     R.nrhs = n;
     std::vector<SlotInit> slots(n);
     for (int r = 0; r < n; ++r) {
@@ -1106,7 +1105,11 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
         if (rc) return rc;
         if (R.persist && *(const int*)(h + e->N) != 0) {
             // a wait of the resident kernel ran out (another process on the
-            // device): start over with a kernel per stage
+            // device, compute units masked off): start over with a kernel per
+            // stage, and do not try again in this context, where every solve
+            // would pay for the wait
+            e->ctx->resident_off = 1;
+            e->ctx->resident_gave_up += 1;
             RCK(hipStreamSynchronize(stream));
             RCK(hipMemsetAsync(e->st + e->N, 0, kAbortBytes, stream));
             e->tag = 0;
@@ -1283,6 +1286,21 @@ int time_iteration_kernels(stag_engine* e, const HopTune& t, int nrhs, int reps,
 }  // namespace stag
 
 using namespace stag;
+
+extern "C" int stag_resident_wait(stag_ctx* ctx, double seconds) {
+    if (!ctx) return STAG_EINVAL;
+    if (!(seconds <= 1e6)) return set_error(ctx, STAG_EINVAL, "stag_resident_wait: bad argument");
+    ctx->resident_wait = seconds < 0 ? -1 : (long long)(seconds * 1e8);  // ticks of 10 ns
+    ctx->resident_off = 0;
+    return STAG_OK;
+}
+
+extern "C" int stag_resident_counts(const stag_ctx* ctx, int64_t* solves, int64_t* gave_up) {
+    if (!ctx || !solves || !gave_up) return STAG_EINVAL;
+    *solves = ctx->resident_solves.load();
+    *gave_up = ctx->resident_gave_up.load();
+    return STAG_OK;
+}
 
 extern "C" int stag_time_kernels(stag_ctx* ctx, const stag_gauge* g, int prec, int nrhs, int reps,
                                  double* us_out) {

@@ -285,6 +285,38 @@ static void temporaries() {
     stag_destroy(c);
 }
 
+// A resident kernel whose waits run out: the solve starts over with a kernel per
+// stage (from its guess too), and later solves of the context do not try again
+// until they are told to.
+static void resident_gives_up() {
+    for (int n : {1, 3}) {
+        stag_ctx* c = nullptr;
+        CHECK(stag_create(0, 0, &c) == STAG_OK);
+        stag_gauge* g = make_gauge(c, k88, STAG_MASK_F64 | STAG_MASK_F32);
+        Solve s;
+        s.n = n;
+        int64_t solves = 0, gave_up = 0;
+        CHECK(solve(c, g, s) == STAG_OK);
+        CHECK(stag_resident_counts(c, &solves, &gave_up) == STAG_OK && solves == 1 && gave_up == 0);
+        CHECK(stag_resident_wait(c, -1.0) == STAG_OK);
+        const int stages = ctl.stage;
+        CHECK(solve(c, g, s) == STAG_OK);
+        CHECK(ctl.stage > stages);
+        CHECK(stag_resident_counts(c, &solves, &gave_up) == STAG_OK && solves == 2 && gave_up == 1);
+        const int launched = ctl.persist;
+        for (int prec : {STAG_F32, STAG_F64}) {
+            s.prec = prec;
+            CHECK(solve(c, g, s) == STAG_OK);
+        }
+        CHECK(ctl.persist == launched);
+        CHECK(stag_resident_wait(c, 2.0) == STAG_OK);
+        CHECK(solve(c, g, s) == STAG_OK);
+        CHECK(ctl.persist > launched);
+        CHECK(stag_resident_counts(c, &solves, &gave_up) == STAG_OK && solves == 3 && gave_up == 1);
+        stag_destroy(c);
+    }
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
@@ -292,6 +324,7 @@ int main(int argc, char** argv) {
         {"budget", budget},
         {"failed_sync", failed_sync},
         {"temporaries", temporaries},
+        {"resident_gives_up", resident_gives_up},
         {"small_same_for_blocks", small_same_for_blocks},
         {"small_without_graphs", small_without_graphs},
     };

@@ -101,3 +101,53 @@ def test_resident_mixed_variants(stag, ctx, variant):
     assert rc1 == rc2 and st1 == st2
     assert np.array_equal(x1, x2)
     g.destroy()
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("r12", [False, True])
+def test_which_lattices_are_solved_in_the_resident_kernel(stag, ctx, inner, r12):
+    """Up to 65536 sites per parity, plain CG up to 32768 (two lanes per site), and
+    no more workgroups than compute units; small_lattice=False never."""
+    for L, n in [((4, 4, 4, 6), 16), ((6, 6, 6, 6), 1), ((8, 6, 10, 14), 2), ((16, 16, 16, 16), 1),
+                 ((16, 16, 16, 18), 1), ((16, 16, 16, 32), 1), ((16, 16, 16, 32), 2),
+                 ((16, 16, 16, 34), 1)]:
+        vh = L[0] * L[1] * L[2] * L[3] // 2
+        fits = n * vh <= (32768 if inner == "f64" else 65536)
+        g = ctx.gauge(L, links(L, "exp", 58, 0.2), precisions=("f64", "f32", "f16s"), r12=r12)
+        fb = ctx.field(g, 0, "f64", n).load(synth.gaussian_rhs(L, n, 59))
+        fx = ctx.field(g, 0, "f64", n)
+        for small in (True, False):
+            before = stag.stag_resident_counts(ctx)
+            rc, st = stag.stag_cg_solve(ctx, g, [0.5] * n, fb, fx,
+                                        stag.cg_params(tol=1e-6, inner=inner, small_lattice=small))
+            after = stag.stag_resident_counts(ctx)
+            assert rc == 0
+            assert after == (before[0] + (1 if fits and small else 0), before[1]), (L, n, small)
+        for o in (fb, fx, g):
+            o.destroy()
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("n,guess", [(1, False), (3, False), (1, True), (3, True)])
+def test_waits_that_run_out_fall_back_to_stages(stag, inner, n, guess):
+    """With no wait granted every workgroup leaves at once; the solve starts over
+    with a kernel per stage and has its bits, also from a guess. Later solves of
+    the context keep to stages until the wait is set again, and are right."""
+    L = (8, 8, 8, 8)
+    U = links(L, "exp", 60, 0.3)
+    b = synth.gaussian_rhs(L, n, 61)
+    x0 = synth.gaussian_rhs(L, n, 62) if guess else None
+    masses = [0.2, 0.3, 0.25][:n]
+    with stag.Context(0) as c:
+        g = c.gauge(L, U, precisions=("f64", "f32", "f16s"))
+        stag.stag_resident_wait(c, -1.0)
+        (rc1, st1, x1), (rc2, st2, x2) = both(stag, c, g, b, masses, x0=x0, tol=1e-9, inner=inner)
+        assert stag.stag_resident_counts(c) == (1, 1)
+        assert rc1 == rc2 == 0 and st1 == st2 and np.array_equal(x1, x2)
+        (rc1, st1, x1), _ = both(stag, c, g, b, masses, x0=x0, tol=1e-9, inner=inner)
+        assert stag.stag_resident_counts(c) == (1, 1)
+        assert rc1 == 0 and np.array_equal(x1, x2)
+        stag.stag_resident_wait(c, 2.0)
+        (rc1, st1, x1), _ = both(stag, c, g, b, masses, x0=x0, tol=1e-9, inner=inner)
+        assert stag.stag_resident_counts(c) == (2, 1)
+        assert rc1 == 0 and st1 == st2 and np.array_equal(x1, x2)
