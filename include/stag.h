@@ -264,11 +264,13 @@ typedef struct stag_cg_params {
                           call fit on the device together, take a group of resident
                           workgroups per right-hand side, with the bits of the
                           kernel-per-stage solver (above 648 sites with use_graph
-                          only; a second such solve in the process at the same time
-                          on the same device takes the kernel-per-stage solver,
-                          and so does every solve of a context after the waits
-                          inside such a kernel ran out once: stag_resident_wait).
-                          Eq.5 gauges only.
+                          only). Such solves of one process share a device as long
+                          as their workgroups (one per 64 to 256 sites and
+                          right-hand side) number 32 together; one that has no
+                          room beside the others takes the kernel-per-stage
+                          solver, as does every solve of a context after the
+                          waits inside such a kernel ran out once
+                          (stag_resident_wait). Eq.5 gauges only.
                           0: always the kernel-per-stage solver */
 } stag_cg_params;
 

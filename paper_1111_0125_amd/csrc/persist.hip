@@ -515,8 +515,8 @@ hipError_t launch_persist(int prec, int S, bool r12, const PersistArgs& a, hipSt
     PersistArgs arg = a;
     void* args[] = {&arg};
     const int grid = a.one_xcd ? 8 * a.blocks * ((a.nrhs + 7) / 8) : a.nrhs * a.blocks;
-    // The caller keeps the grid within one block per compute unit and such
-    // kernels one at a time; whatever else runs on the device ends by itself, so
+    // The caller keeps the grids of all such kernels within one block per compute
+    // unit (ResidentHold); whatever else runs on the device ends by itself, so
     // every block becomes resident. (A cooperative launch would check the same
     // and costs 20 us of idle device around each launch.)
     return hipLaunchKernel(fn, dim3((uint32_t)grid), dim3(kBlock), args, 0, stream);

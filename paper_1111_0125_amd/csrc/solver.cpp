@@ -783,12 +783,36 @@ constexpr int kPersistIters = 1024;
 // Rounds (one launch and its fix-up) between polls.
 constexpr int kPersistRounds = 3;
 
-// One resident kernel at a time per device and process: two of them, each
-// holding part of the compute units, would wait for each other.
-static std::mutex& persist_mutex(int device) {
-    static std::mutex mu[64];
-    return mu[device & 63];
+// The compute units that resident kernels hold, per device and process. Two of
+// them that are each only partly on the device would wait for each other, so
+// one is let in beside others only when all their workgroups together, at one
+// per compute unit, fit on any single XCD (32 units): then each is wholly
+// resident wherever its workgroups land. A larger one runs alone.
+struct ResidentUnits {
+    std::mutex mu;
+    int used = 0;
+};
+static ResidentUnits& resident_units(int device) {
+    static ResidentUnits u[64];
+    return u[device & 63];
 }
+struct ResidentHold {
+    ResidentUnits& u;
+    int held = 0;
+    explicit ResidentHold(int device) : u(resident_units(device)) {}
+    ~ResidentHold() { release(); }
+    bool take(int blocks, int cus) {
+        std::lock_guard<std::mutex> lk(u.mu);
+        if (u.used != 0 && u.used + blocks > cus / 8) return false;
+        u.used += held = blocks;
+        return true;
+    }
+    void release() {
+        std::lock_guard<std::mutex> lk(u.mu);
+        u.used -= held;
+        held = 0;
+    }
+};
 
 // Lanes per site of the resident kernel for n right-hand sides, 0: not here
 // (the groups of blocks have to be resident together, one block per compute
@@ -1053,7 +1077,7 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
                  void* x_out, size_t x_rs, const stag_cg_params& p, stag_cg_stats* stats,
                  hipStream_t stream, bool escalating) {
     // held while the resident kernel is in use (below), and until it has ended
-    std::unique_lock<std::mutex> resident(persist_mutex(e->ctx->device), std::defer_lock);
+    ResidentHold resident(e->ctx->device);
     // a solve that fails leaves nothing running on the engine, which is lent to
     // the next one
     WaitAtExit wait{stream};
@@ -1071,11 +1095,11 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
     EngineRun R;
     run_init(R, e, stream, e->b64, e->rs64, K, p.use_graph != 0);
     R.variant = e->prec != P64 ? p.mixed_variant : MIXED_CARRY;
-    // small lattices: the iterations in a resident kernel, unless another solve
-    // of this process has one on the device (the results are the same bits)
+    // small lattices: the iterations in a resident kernel, unless others of this
+    // process leave it no room (the results are the same bits)
     if (p.small_lattice != 0 && !R.timed && (R.use_graph || e->Vh <= kNoGraphSites) &&
         (R.persist = persist_lanes(e, n)) != 0 &&
-        !resident.try_lock())
+        !resident.take((int)hop_blocks(e->Vh, R.persist) * n, e->ctx->cus))
         R.persist = 0;
     if (R.persist) e->ctx->resident_solves += 1;
     R.nrhs = n;
@@ -1113,7 +1137,7 @@ int engine_solve(stag_engine* e, int n, const double* mass, const void* b64, siz
             RCK(hipStreamSynchronize(stream));
             RCK(hipMemsetAsync(e->st + e->N, 0, kAbortBytes, stream));
             e->tag = 0;
-            resident.unlock();
+            resident.release();
             stag_cg_params q = p;
             q.small_lattice = 0;
             return engine_solve(e, n, mass, b64, b_rs, x_out, x_rs, q, stats, stream, escalating);

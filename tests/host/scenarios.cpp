@@ -317,6 +317,42 @@ static void resident_gives_up() {
     }
 }
 
+// Solves of several threads at once, each with a context of its own: small ones
+// run in resident kernels beside each other, never with more workgroups than one
+// XCD has units; a large one runs alone or with a kernel per stage.
+static void resident_together() {
+    ctl.kernel_ms = 20;
+    auto run = [](const Lattice& l, int threads, int64_t* resident) {
+        std::vector<std::thread> th;
+        std::atomic<int64_t> sum{0};
+        for (int k = 0; k < threads; ++k)
+            th.emplace_back([&] {
+                stag_ctx* c = nullptr;
+                CHECK(stag_create(0, 0, &c) == STAG_OK);
+                stag_gauge* g = make_gauge(c, l, STAG_MASK_F64);
+                Solve s;
+                s.prec = STAG_F64;
+                for (int i = 0; i < 3; ++i) CHECK(solve(c, g, s) == STAG_OK);
+                int64_t n = 0, gave_up = 0;
+                CHECK(stag_resident_counts(c, &n, &gave_up) == STAG_OK && gave_up == 0);
+                sum += n;
+                stag_destroy(c);
+            });
+        for (auto& t : th) t.join();
+        *resident = sum;
+    };
+    int64_t n = 0;
+    run(k44, 6, &n);  // 2 workgroups each
+    CHECK(n == 18 && ctl.persist_most >= 2 && ctl.blocks_most <= 32);
+    ctl.persist_most = ctl.blocks_most = 0;
+    run(k66, 6, &n);  // 11 each: two at a time
+    CHECK(n >= 3 && ctl.persist_most <= 2 && ctl.blocks_most <= 32);
+    ctl.persist_most = ctl.blocks_most = 0;
+    run(k16, 3, &n);  // 256: alone
+    CHECK(n >= 1 && ctl.persist_most == 1);
+    ctl.kernel_ms = 0;
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
@@ -325,6 +361,7 @@ int main(int argc, char** argv) {
         {"failed_sync", failed_sync},
         {"temporaries", temporaries},
         {"resident_gives_up", resident_gives_up},
+        {"resident_together", resident_together},
         {"small_same_for_blocks", small_same_for_blocks},
         {"small_without_graphs", small_without_graphs},
     };

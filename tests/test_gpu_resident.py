@@ -2,6 +2,8 @@
 the kernel-per-stage solver: the stages, their rounding and the reduction
 order are the same, so the iterates are the same bits."""
 
+import threading
+
 import numpy as np
 import pytest
 
@@ -151,3 +153,42 @@ def test_waits_that_run_out_fall_back_to_stages(stag, inner, n, guess):
         (rc1, st1, x1), _ = both(stag, c, g, b, masses, x0=x0, tol=1e-9, inner=inner)
         assert stag.stag_resident_counts(c) == (2, 1)
         assert rc1 == 0 and st1 == st2 and np.array_equal(x1, x2)
+
+
+def test_small_solves_of_several_threads_share_the_device(stag):
+    """Four threads, each with a context of its own: 2 to 6 workgroups a solve, so
+    all of them fit beside each other. Every solve starts in a resident kernel,
+    no wait runs out, and each has the bits of the solve alone."""
+    jobs = [((4, 4, 4, 4), "f64", False), ((6, 6, 6, 6), "f32", True), ((4, 4, 4, 4), "f64", True),
+            ((4, 4, 4, 8), "f32", False)]
+    solves, got, errors = 6, {}, []
+
+    def work(key, job, n):
+        try:
+            L, inner, r12 = job
+            with stag.Context(0) as c:
+                g = c.gauge(L, links(L, "haar", 63), precisions=("f64", "f32"), r12=r12)
+                fb = c.field(g, 0, "f64", 1).load(synth.gaussian_rhs(L, 1, 64))
+                fx = c.field(g, 0, "f64", 1)
+                xs = []
+                for _ in range(n):
+                    rc, st = stag.stag_cg_solve(c, g, [0.05], fb, fx, stag.cg_params(tol=1e-10, inner=inner))
+                    assert rc == 0
+                    xs.append(fx.store())
+                got[key] = (xs, stag.stag_resident_counts(c))
+        except BaseException as e:
+            errors.append(e)
+
+    for k, job in enumerate(jobs):
+        work(("alone", k), job, 1)
+    threads = [threading.Thread(target=work, args=(("together", k), job, solves)) for k, job in enumerate(jobs)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k in range(len(jobs)):
+        xs, counts = got["together", k]
+        assert counts == (solves, 0)
+        for x in xs:
+            assert np.array_equal(x, got["alone", k][0][0])
