@@ -317,7 +317,8 @@ int stag_cg_solve(stag_ctx* ctx, const stag_gauge* gauge, const double* mass,
 
 /* Resident kernels of small lattices (small_lattice above): their workgroups
  * wait for each other inside the kernel, which needs all of them on the
- * device. A wait that runs out (2 s; another process on the device can hold
+ * device; kernels of other streams that find no free compute unit wait for the
+ * end of a launch (on 16^4 and 16^3 x 32 about 0.5 ms). A wait that runs out (2 s; another process on the device can hold
  * compute units) ends the kernel; the solve starts over with a kernel per
  * stage, and so does every later one of the context.
  * stag_resident_wait: sets the longest such wait in seconds (< 0: every wait

@@ -776,10 +776,16 @@ static int launch_block_graphs(EngineRun& R, int busy, int K) {
 
 // ------------------------------------------------------------------ resident iterations
 
-// Iterations per launch of the resident kernel: a fix-up comes due every few
-// tens of iterations in mixed CG, so this only bounds how long one launch
-// keeps its compute units to itself (about 10 us an iteration).
+// Iterations per launch of the resident kernel. A launch keeps its compute units
+// to itself (10 to 16 us an iteration); with most of the device's in use,
+// kernels of other streams wait for its end, so there it is kept short. A
+// 4^4 operator call with its copy back beside 16^4 plain CG / 16^3 x 32 fp32
+// solves (median, and the solve alone): 64 iterations a launch 0.51 / 0.29 ms
+// (51.8 / 33.6 ms), 128 1.5 / 1.1 (51.2 / 33.3), 256 3.6 / 2.8 (50.8 / 33.4), 1024
+// 16.1 / 3.4 (50.7 / 33.2; in mixed CG the updates end a launch before); with a
+// kernel per stage 0.07 (82.5 / 55.3).
 constexpr int kPersistIters = 1024;
+constexpr int kPersistItersWide = 64;
 // Rounds (one launch and its fix-up) between polls.
 constexpr int kPersistRounds = 3;
 
@@ -860,7 +866,7 @@ static int enqueue_persist_rounds(EngineRun& R, int nk) {
     a.nrhs = R.nrhs;
     a.blocks = (int)hop_blocks(e->Vh, R.persist);
     a.one_xcd = a.blocks * ((R.nrhs + 7) / 8) <= 32;
-    a.max_iters = kPersistIters;
+    a.max_iters = 2 * a.blocks * a.nrhs > e->ctx->cus ? kPersistItersWide : kPersistIters;
     a.limit = e->ctx->resident_wait;
     Ctx c{e, Issue{R.s}, nk, false, R.variant};
     for (int k = 0; k < kPersistRounds; ++k) {
@@ -869,7 +875,7 @@ static int enqueue_persist_rounds(EngineRun& R, int nk) {
             e->tag = 2;
         }
         a.tag = e->tag;
-        e->tag += 2u * kPersistIters + 2;
+        e->tag += 2u * (uint32_t)a.max_iters + 2;
         RCK(launch_persist(P, R.persist, g->r12, a, R.s));
         RCK(mixed ? enqueue_update(c) : enqueue_check(c));
     }

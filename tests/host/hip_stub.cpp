@@ -371,7 +371,6 @@ hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t s) {
     Exec* x = (Exec*)e;
     if (x->dead) violation("a destroyed graph is launched");
     if (ctl.fail_graph_launch > 0 && --ctl.fail_graph_launch == 0) return hipErrorUnknown;
-    ctl.graph_launches += 1;
     x->pending += 1;
     stream_of(s)->push({[x] { for (auto& f : x->nodes) f(); }, [x] { x->pending -= 1; }, 20});
     return hipSuccess;
@@ -438,6 +437,7 @@ hipError_t launch_finalize(int N, const Reduce& R, unsigned mask, const Issue& i
 
 hipError_t launch_persist(int prec, int, bool, const PersistArgs& a, hipStream_t s) {
     ctl.persist += 1;
+    if (a.max_iters > ctl.persist_iters) ctl.persist_iters = a.max_iters;
     return issue(Issue{s}, [=] {
         const int blocks = a.nrhs * a.blocks;
         const int now = ctl.persist_now += 1, nb = ctl.blocks_now += blocks;

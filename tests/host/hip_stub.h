@@ -27,7 +27,7 @@ struct Control {
     std::atomic<int> persist{0}, tiny{0}, stage{0};  // launches: resident, one workgroup, per stage
     std::atomic<int> persist_now{0}, persist_most{0};  // resident kernels running, and the most
     std::atomic<int> blocks_now{0}, blocks_most{0};  // their workgroups at one time
-    std::atomic<int> graph_launches{0};
+    std::atomic<int> persist_iters{0};               // the most iterations given to one launch
 };
 extern Control ctl;
 

@@ -353,6 +353,21 @@ static void resident_together() {
     ctl.kernel_ms = 0;
 }
 
+// A resident kernel that holds most of the compute units leaves them after a
+// bounded number of iterations.
+static void resident_launches_are_short() {
+    for (const Lattice& l : {k16, Lattice{{16, 16, 16, 32}}, k88}) {
+        stag_ctx* c = nullptr;
+        CHECK(stag_create(0, 0, &c) == STAG_OK);
+        stag_gauge* g = make_gauge(c, l, STAG_MASK_F64 | STAG_MASK_F32);
+        ctl.persist_iters = 0;
+        Solve s;
+        CHECK(solve(c, g, s) == STAG_OK);
+        CHECK(ctl.persist_iters > 0 && (l.vh() <= 16384 || ctl.persist_iters <= 64));
+        stag_destroy(c);
+    }
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
@@ -362,6 +377,7 @@ int main(int argc, char** argv) {
         {"temporaries", temporaries},
         {"resident_gives_up", resident_gives_up},
         {"resident_together", resident_together},
+        {"resident_launches_are_short", resident_launches_are_short},
         {"small_same_for_blocks", small_same_for_blocks},
         {"small_without_graphs", small_without_graphs},
     };
