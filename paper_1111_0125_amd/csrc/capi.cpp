@@ -225,21 +225,6 @@ static bool wide_blocks(const stag_gauge* g, int prec) {
     return g->npairs == 8 || (prec == P32 && g->g.Vh >= 65536);
 }
 
-// Shape of the operator calls: fp32 with one right-hand side takes two lanes per
-// site on lattices of 131072 sites per parity or more unless a shape was set or
-// tuned (import, A, export, us: 24^3 x 48 75.8 against 78.9 with one lane, full
-// links 96.1 and 99.2; 32^3 x 64 210.6 and 212.0); in solves, where the stages
-// follow each other with other vectors between them, one lane stays the faster
-// (24^3 x 48 63.2 against 65.7 ms, 32^3 x 64 86.6 against 95.6).
-static HopTune operator_tune(stag_ctx* ctx, int prec, int N, uint32_t Vh, int npairs) {
-    HopTune t = get_tune(ctx, prec, N, Vh, npairs);
-    if (prec == P32 && N == 1 && npairs == 4 && Vh >= 131072) {
-        std::lock_guard<std::mutex> lk(ctx->tune_mu);
-        if (!ctx->tune.count(tune_key(prec, N, Vh, npairs))) t.S1 = t.S2 = 2;
-    }
-    return t;
-}
-
 void set_tune(stag_ctx* ctx, int prec, int N, uint32_t Vh, int npairs, const HopTune& t) {
     std::lock_guard<std::mutex> lk(ctx->tune_mu);
     ctx->tune[tune_key(prec, N, Vh, npairs)] = t;
@@ -767,7 +752,7 @@ int stag_dslash(stag_ctx* ctx, const stag_gauge* g, const stag_field* in, stag_f
     int done = 0;
     while (done < in->nrhs) {
         const int Nk = fit_n(in->nrhs - done, wide_blocks(g, in->prec));
-        HopTune t = operator_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
+        HopTune t = get_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
         const char* ip = (const char*)in->data + (size_t)done * in->rs;
         char* op = (char*)out->data + (size_t)done * out->rs;
         HIPCK(ctx, enqueue_hop(g, in->prec, t.S1, Nk, EPI_PLAIN, t, ip, in->rs, op, out->rs,
@@ -808,7 +793,7 @@ static int apply_A_stages(stag_ctx* ctx, const stag_gauge* g, const double* mass
         const int Nk = fit_n(in->nrhs - done, wide_blocks(g, in->prec));
         double m2[kMaxN] = {0};
         for (int r = 0; r < Nk; ++r) m2[r] = mass[done + r] * mass[done + r];
-        HopTune tu = operator_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
+        HopTune tu = get_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
         const char* ip = (const char*)in->data + (size_t)done * in->rs;
         char* tp = (char*)t + (size_t)done * in->rs;
         char* op = (char*)out->data + (size_t)done * out->rs;
