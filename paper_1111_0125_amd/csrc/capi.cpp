@@ -215,14 +215,22 @@ HopTune get_tune(stag_ctx* ctx, int prec, int N, uint32_t Vh, int npairs) {
     return t;
 }
 
-// Operator calls of 12 and more right-hand sides: whether blocks of 12 and 16
-// are taken whole (fit_n): with the improved operator, and in fp32 from 65536
-// sites per parity on (import, A, export of 12 RHS with full links, us, whole
-// against 8 + 4: 20 x 18 x 22 x 30 158 and 172; 20 x 18 x 18 x 22, 71280 sites,
-// 133 and 138; 14 x 16 x 16 x 20, 35840 sites, 99 and 77; the whole blocks of the
-// last two with the kernels before the links lay in tiles).
-static bool wide_blocks(const stag_gauge* g, int prec) {
-    return g->npairs == 8 || (prec == P32 && g->g.Vh >= 65536);
+// Whether operator calls of 12 to 15 right-hand sides take a block of 12 (import,
+// A, export of 12, us, whole against 8 + 4). A block reads the links once, but its
+// gathers go over the vectors of 12 right-hand sides: in fp32 that pays while
+// those still fit the caches, up to about 40 MB of them, and not on lattices
+// of few workgroups: 12-parameter / full links 65536 sites 93.8 / 100.4 and 81.5 /
+// 85.2, 69984 104.6 / 109.3 and 108.7 / 118.1, 73728 97.0 / 101.8 and 107.7 / 117.6,
+// 118800 124.4 / 129.8 and 127.7 / 139.9, 131072 133.3 / 140.7 and 138.3 / 150.9,
+// 160000 209.6 / 218.2 and 184.9 / 198.8, 331776 371.0 / 386.7 and 349.2 / 379.8. The
+// improved operator, with twice the links to read, in fp32 10368 sites 76.2 and
+// 77.3, 35840 97.7 and 120.1, 118800 196.8 and 231.6, in fp64 94.4 and 96.3, 181.5 and
+// 176.9, 400.0 and 407.5. fp64 and fp16 otherwise 8 + 4: 71280 sites 196.3 and 168.2,
+// 103.4 and 100.9, improved fp16 177.1 and 141.2. 16 are two blocks of 8 everywhere:
+// fp32 71280 sites 199.7 whole, 129.2; 331776 680.9 and 437.7; improved 231.7 and 204.3.
+static bool twelve_whole(const stag_gauge* g, int prec) {
+    if (g->npairs == 8) return prec != P16S;
+    return prec == P32 && g->g.Vh > 65536 && g->g.Vh < 147456;
 }
 
 void set_tune(stag_ctx* ctx, int prec, int N, uint32_t Vh, int npairs, const HopTune& t) {
@@ -751,7 +759,7 @@ int stag_dslash(stag_ctx* ctx, const stag_gauge* g, const stag_field* in, stag_f
     // exactly nrhs: a spare slot without state would be processed too
     int done = 0;
     while (done < in->nrhs) {
-        const int Nk = fit_n(in->nrhs - done, wide_blocks(g, in->prec));
+        const int Nk = fit_n(in->nrhs - done, twelve_whole(g, in->prec));
         HopTune t = get_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);
         const char* ip = (const char*)in->data + (size_t)done * in->rs;
         char* op = (char*)out->data + (size_t)done * out->rs;
@@ -790,7 +798,7 @@ static int apply_A_stages(stag_ctx* ctx, const stag_gauge* g, const double* mass
                           const stag_field* in, stag_field* out, void* t, hipStream_t s) {
     int done = 0;
     while (done < in->nrhs) {
-        const int Nk = fit_n(in->nrhs - done, wide_blocks(g, in->prec));
+        const int Nk = fit_n(in->nrhs - done, twelve_whole(g, in->prec));
         double m2[kMaxN] = {0};
         for (int r = 0; r < Nk; ++r) m2[r] = mass[done + r] * mass[done + r];
         HopTune tu = get_tune(ctx, in->prec, Nk, g->g.Vh, g->npairs);

@@ -147,10 +147,10 @@ inline int pick_n(int n) {
 // The largest kernel block for the first of n right-hand sides without spare
 // slots: calls of more than 8 run as blocks of 8 and the rest (per right-hand
 // side a block of 12 or 16 costs more than one of 8: import, A, export of 12 RHS on
-// 12^4 fp32 65 us against 85). The operator calls of the improved operator keep
-// blocks of 12 and 16 (12 RHS on 20 x 18 x 22 x 30 fp32: 226 us against 257 as 8 + 4).
-inline int fit_n(int n, bool wide = false) {
-    if (wide && n >= 12) return n >= 16 ? 16 : 12;
+// 12^4 fp32 59 us against 78 whole). twelve: 12 to 15 as a block of 12 and the
+// rest, where that is the faster for operator calls (capi.cpp).
+inline int fit_n(int n, bool twelve = false) {
+    if (twelve && n >= 12 && n < 16) return 12;
     return n >= 8 ? 8 : n >= 4 ? 4 : n;
 }
 

@@ -79,3 +79,28 @@ def test_block_solve_groups_equal_singles(stag, ctx, n):
         assert np.array_equal(x1.store()[0], x[k]), k
     for o in (fb, fx, f1, x1, g):
         o.destroy()
+
+
+@pytest.mark.parametrize("n", [12, 13, 16])
+@pytest.mark.parametrize("form", ["full", "r12", "improved"])
+def test_blocks_of_twelve_equal_singles(stag, ctx, n, form):
+    """fp32 on 69984 sites per parity, where 12 to 15 right-hand sides take a block
+    of 12 whole and 16 two of 8 (the improved operator on any lattice)."""
+    L = (18, 18, 18, 24)
+    U = links(L, "exp", 86, 0.4)
+    lng = None
+    if form == "improved":
+        U, lng = synth.naik_links(U, fat_noise=0.05, seed=87)
+    g = ctx.gauge(L, U, precisions=("f32",), r12=form == "r12", long=lng)
+    v = synth.gaussian_rhs(L, n, 88)
+    masses = [0.05 * (k + 1) for k in range(n)]
+    fi, fo = ctx.field(g, 0, "f32", n).load(v), ctx.field(g, 0, "f32", n)
+    stag.stag_apply_A(ctx, g, masses, fi, fo)
+    got = fo.store()
+    f1, o1 = ctx.field(g, 0, "f32", 1), ctx.field(g, 0, "f32", 1)
+    for k in sorted({0, 7, 8, 11, n - 1}):
+        f1.load(v[k:k + 1])
+        stag.stag_apply_A(ctx, g, masses[k:k + 1], f1, o1)
+        assert np.array_equal(o1.store()[0], got[k]), k
+    for o in (fi, fo, f1, o1, g):
+        o.destroy()
