@@ -382,10 +382,12 @@ int stag_solver_config(stag_ctx* ctx, int slots_per_batch, int graph_k, int queu
  * gauges of Eq.5's operator, or with STAG_TUNE_IMPROVED or-ed into prec by
  * gauges of the improved operator. stag_tune: time the solver's own iteration
  * kernels (see stag_time_kernels) in every shape on the gauge's actual
- * links and keep the fastest for gauges of its kind (Eq.5 or improved) (synchronous; uses a solver workspace for nrhs right-hand
- * sides, allocated if none is free). best / best_ms may be NULL; best_ms is
- * the time of the two hop stages in milliseconds. Errors: EINVAL, ENOMEM,
- * EDEVICE.
+ * links and keep the fastest for gauges of its kind (Eq.5 or improved), for
+ * every kernel size that solves and operator calls of nrhs right-hand sides
+ * use: iterations of more than 4 run as groups of 8, 4, 3, 2 and 1 (synchronous; uses
+ * a solver workspace of each size, allocated if none is free). best / best_ms
+ * may be NULL: the shape of the first group, and the time of the two hop
+ * stages of all groups in milliseconds. Errors: EINVAL, ENOMEM, EDEVICE.
  */
 #define STAG_TUNE_IMPROVED (1 << 8)
 
@@ -428,7 +430,7 @@ int stag_timing_enable(stag_ctx* ctx, int on);
 /* stag_time_kernels: average execution time in microseconds of the three
  * kernels of one CG iteration exactly as stag_cg_solve launches them (same
  * buffers, launch shape and arithmetic) for `prec` (STAG_F64: plain CG, else
- * mixed) and nrhs right-hand sides: us[0] = D_oe stage (with the deferred
+ * mixed) and nrhs right-hand sides (summed over the groups that they run in): us[0] = D_oe stage (with the deferred
  * direction update and the finalisation of the previous |r|^2), us[1] = D_eo
  * stage with m^2 update and <d, A d>, us[2] = fused update with |r|^2 (and
  * the finalisation of alpha). Blocks of 8 or more right-hand sides, and

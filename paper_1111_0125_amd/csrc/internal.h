@@ -252,6 +252,12 @@ void set_tune(stag_ctx* ctx, int prec, int N, uint32_t Vh, int npairs, const Hop
 // Engines (solver.cpp)
 int engine_acquire(stag_ctx* ctx, const stag_gauge* g, int prec, int N, stag_engine** out);
 void engine_release(stag_engine* e);
+// The groups that the iterations of the slots below `busy` run in, each as
+// kernels of n right-hand sides starting at slot g0.
+struct Group {
+    int g0, n;
+};
+std::vector<Group> slot_groups(uint32_t Vh, int busy);
 // Whether the iteration kernels of e (nk right-hand sides per kernel)
 // finalise reductions at their start (small lattices) or leave it to a
 // one-block kernel (large ones).

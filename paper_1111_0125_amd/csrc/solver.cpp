@@ -16,6 +16,7 @@
 // the other slots or on the kernel's block size N, so a solve gives the same
 // bits alone and in a mix. stag_cg_solve runs one batch of slots to the
 // end; the serving loop (serve.cpp) keeps slots busy continuously.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -202,6 +203,21 @@ constexpr size_t kFuseMaxPartials = 2048;
 // one RHS an fp16+scale iteration takes 17 % less and an fp32 one 1 % less).
 constexpr uint32_t kXpayMinSites = 131072;
 constexpr int kXpayMinRhs = 8;
+
+// Kernels serve groups of 8, 4, 3, 2 or 1 slots, each group its own chain, so
+// that no kernel has idle slots (its fast loop needs every one active) and none
+// more than 8 (per right-hand side an iteration costs less with 8 per kernel
+// than with 12 or 16, whose neighbour gathers miss the caches more). Below
+// kXpayMinSites sites per parity 5 to 8 slots run as two groups of 4, which
+// overlap (ms per solve, 16^3 x 32: 8 RHS 48.6 against 52.3 as one group, 5 RHS 42.2
+// against 51.3 as 4 + 1; on 24^3 x 48 8 RHS 415 against 350). 12 RHS as 8 + 4: 68.5
+// against 82.8 as three groups on 16^3 x 32, 501 against 506 on 24^3 x 48.
+std::vector<Group> slot_groups(uint32_t Vh, int busy) {
+    if (busy > 4 && busy <= 8 && Vh < kXpayMinSites) return {{0, 4}, {4, 4}};
+    std::vector<Group> v;
+    for (int g0 = 0; g0 < busy; g0 += v.back().n) v.push_back({g0, fit_n(busy - g0)});
+    return v;
+}
 
 bool fuse_finalize(const stag_engine* e, int nk) {
     return (size_t)vec_blocks(e->Vh) * (size_t)nk <= kFuseMaxPartials;
@@ -540,24 +556,6 @@ void slot_view(const stag_engine* e, int g0, int nk, stag_engine* v) {
     v->tune_64 = get_tune(e->ctx, P64, nk, e->Vh, e->gauge->npairs);
 }
 
-// Kernels serve groups of 8, 4, 3, 2 or 1 slots, each group its own chain, so
-// that no kernel has idle slots (its fast loop needs every one active) and none
-// more than 8 (per right-hand side an iteration costs less with 8 per kernel
-// than with 12 or 16, whose neighbour gathers miss the caches more). Below
-// kXpayMinSites sites per parity 5 to 8 slots run as two groups of 4, which
-// overlap (ms per solve, 16^3 x 32: 8 RHS 48.6 against 52.3 as one group, 5 RHS 42.2
-// against 51.3 as 4 + 1; on 24^3 x 48 8 RHS 415 against 350). 12 RHS as 8 + 4: 68.5
-// against 82.8 as three groups on 16^3 x 32, 501 against 506 on 24^3 x 48.
-struct Group {
-    int g0, n;
-};
-std::vector<Group> slot_groups(const stag_engine* e, int busy) {
-    if (busy > 4 && busy <= 8 && e->Vh < kXpayMinSites) return {{0, 4}, {4, 4}};
-    std::vector<Group> v;
-    for (int g0 = 0; g0 < busy; g0 += v.back().n) v.push_back({g0, fit_n(busy - g0)});
-    return v;
-}
-
 // One block (K iterations with their fix-ups) of the slots [g0, g0 + nk).
 hipError_t enqueue_slots(const Ctx& c, int g0, int nk, int K, int F) {
     if (g0 == 0 && nk == c.nk) return enqueue_block_group(c, K, F);
@@ -572,7 +570,7 @@ hipError_t enqueue_slots(const Ctx& c, int g0, int nk, int K, int F) {
 // One block for the slots below busy, group after group.
 hipError_t enqueue_block(const Ctx& c, int busy, int K, int F) {
     hipError_t err = hipSuccess;
-    for (const Group& g : slot_groups(c.e, busy))
+    for (const Group& g : slot_groups(c.e->Vh, busy))
         if (err == hipSuccess) err = enqueue_slots(c, g.g0, g.n, K, F);
     return err;
 }
@@ -733,11 +731,11 @@ static int get_graph(EngineRun& R, int g0, int nk, int K, hipGraphExec_t* out) {
 // created streams before).
 static int launch_block_graphs(EngineRun& R, int busy, int K) {
     stag_engine* e = R.e;
-    const std::vector<Group> groups = slot_groups(e, busy);
+    const std::vector<Group> groups = slot_groups(e->Vh, busy);
     const int n = (int)groups.size();
     if (n > 1 && (int)e->gstreams.size() < n) {
         if (!e->gfork) RCK(hipEventCreateWithFlags(&e->gfork, hipEventDisableTiming));
-        const size_t want = std::max((size_t)n, slot_groups(e, e->N).size());
+        const size_t want = std::max((size_t)n, slot_groups(e->Vh, e->N).size());
         while (e->gstreams.size() < want) {
             stag_engine::Branch br;
             RCK(hipStreamCreateWithFlags(&br.s, hipStreamNonBlocking));
@@ -1341,10 +1339,18 @@ extern "C" int stag_time_kernels(stag_ctx* ctx, const stag_gauge* g, int prec, i
     if (!(g->mask & (1 << prec)) || !(g->mask & STAG_MASK_F64))
         return set_error(ctx, STAG_EINVAL, "stag_time_kernels: gauge lacks a needed copy");
     DeviceGuard dg(ctx->device);
-    stag_engine* e = nullptr;
-    int rc = engine_acquire(ctx, g, prec, pick_n(nrhs), &e);
-    if (rc) return rc;
-    rc = time_iteration_kernels(e, e->tune_lo, nrhs, reps, us_out);
-    engine_release(e);
-    return rc;
+    // the groups of an iteration one after the other (in a solve they overlap)
+    double sum[3] = {0.0, 0.0, 0.0};
+    for (const Group& q : slot_groups(g->g.Vh, nrhs)) {
+        stag_engine* e = nullptr;
+        int rc = engine_acquire(ctx, g, prec, q.n, &e);
+        if (rc) return rc;
+        double us[3];
+        rc = time_iteration_kernels(e, e->tune_lo, std::min(q.n, nrhs - q.g0), reps, us);
+        engine_release(e);
+        if (rc) return rc;
+        for (int k = 0; k < 3; ++k) sum[k] += us[k];
+    }
+    for (int k = 0; k < 3; ++k) us_out[k] = sum[k];
+    return STAG_OK;
 }

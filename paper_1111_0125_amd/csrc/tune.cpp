@@ -211,33 +211,17 @@ int stag_tune_set(stag_ctx* ctx, int prec, int nrhs, int64_t vh, const stag_tune
     return STAG_OK;
 }
 
-int stag_tune(stag_ctx* ctx, const stag_gauge* g, int prec, int nrhs, stag_tune_cfg* best,
-              double* best_ms) {
-    if (!ctx || !g || prec < 0 || prec > 2 || nrhs < 1 || nrhs > STAG_MAX_RHS)
-        return ctx ? set_error(ctx, STAG_EINVAL, "stag_tune: bad argument") : STAG_EINVAL;
-    if (!(g->mask & (1 << prec)))
-        return set_error(ctx, STAG_EINVAL, "stag_tune: gauge has no copy in precision %d", prec);
-    DeviceGuard dg(ctx->device);
-    const int N = pick_n(nrhs);
+// The launch shape of kernels of N right-hand sides, nrhs of them active, from
+// the table file or by timing the shapes; *loaded says which.
+static int tune_block(stag_ctx* ctx, const stag_gauge* g, int prec, int N, int nrhs, HopTune* best,
+                      double* best_ms, bool* loaded) {
     const uint32_t Vh = g->g.Vh;
     const char* cache = getenv("STAG_TUNE_CACHE");
     const std::string key = cache && *cache ? tune_cache_key(ctx->device, g, prec, N) : std::string();
-    if (!key.empty()) {
-        HopTune t;
-        double ms = 0;
-        if (tune_cache_lookup(cache, key, &t, &ms)) {
-            set_tune(ctx, prec, N, Vh, g->npairs, t);
-            apply_tune_to_engines(ctx);
-            ctx->tune_loaded.fetch_add(1);
-            if (best) {
-                best->S1 = t.S1;
-                best->S2 = t.S2;
-                best->nt = t.nt;
-                best->swizzle = t.swizzle;
-            }
-            if (best_ms) *best_ms = ms;
-            return STAG_OK;
-        }
+    *loaded = !key.empty() && tune_cache_lookup(cache, key, best, best_ms);
+    if (*loaded) {
+        set_tune(ctx, prec, N, Vh, g->npairs, *best);
+        return STAG_OK;
     }
     // time the solver's own iteration kernels (deferred direction update,
     // finalisations at kernel start) on a solver workspace of this shape
@@ -319,16 +303,59 @@ int stag_tune(stag_ctx* ctx, const stag_gauge* g, int prec, int nrhs, stag_tune_
     engine_release(e);
     if (rc) return rc;
     set_tune(ctx, prec, N, Vh, g->npairs, bestT);
-    apply_tune_to_engines(ctx);
-    ctx->tune_measured.fetch_add(1);
-    if (!key.empty()) tune_cache_append(cache, key, bestT, (best1 + best2) * 1e-3);
+    *best = bestT;
+    *best_ms = (best1 + best2) * 1e-3;
+    if (!key.empty()) tune_cache_append(cache, key, bestT, *best_ms);
+    return STAG_OK;
+}
+
+int stag_tune(stag_ctx* ctx, const stag_gauge* g, int prec, int nrhs, stag_tune_cfg* best,
+              double* best_ms) {
+    if (!ctx || !g || prec < 0 || prec > 2 || nrhs < 1 || nrhs > STAG_MAX_RHS)
+        return ctx ? set_error(ctx, STAG_EINVAL, "stag_tune: bad argument") : STAG_EINVAL;
+    if (!(g->mask & (1 << prec)))
+        return set_error(ctx, STAG_EINVAL, "stag_tune: gauge has no copy in precision %d", prec);
+    DeviceGuard dg(ctx->device);
+    // the kernels that the iterations of nrhs right-hand sides run, and the one
+    // of the whole block (operator calls, the start of a solve)
+    struct Size {
+        int N;
+        double ms;
+        HopTune t;
+    };
+    std::vector<Size> sizes;
+    double ms = 0.0;
+    bool measured = false;
+    auto add = [&](int N, int active) -> int {
+        for (const Size& z : sizes)
+            if (z.N == N) {
+                ms += z.ms;
+                return STAG_OK;
+            }
+        Size z{N, 0.0, HopTune()};
+        bool loaded = false;
+        const int rc = tune_block(ctx, g, prec, N, active, &z.t, &z.ms, &loaded);
+        if (rc) return rc;
+        measured |= !loaded;
+        ms += z.ms;
+        sizes.push_back(z);
+        return STAG_OK;
+    };
+    int rc = STAG_OK;
+    for (const Group& q : slot_groups(g->g.Vh, nrhs))
+        if (rc == STAG_OK) rc = add(q.n, std::min(q.n, nrhs - q.g0));
+    const double iteration_ms = ms;
+    if (rc == STAG_OK && sizes[0].N != pick_n(nrhs)) rc = add(pick_n(nrhs), nrhs);
+    if (rc == STAG_OK || !sizes.empty()) apply_tune_to_engines(ctx);
+    if (rc) return rc;
+    (measured ? ctx->tune_measured : ctx->tune_loaded).fetch_add(1);
     if (best) {
-        best->S1 = bestT.S1;
-        best->S2 = bestT.S2;
-        best->nt = bestT.nt;
-        best->swizzle = bestT.swizzle;
+        best->S1 = sizes[0].t.S1;
+        best->S2 = sizes[0].t.S2;
+        best->nt = sizes[0].t.nt;
+        best->swizzle = sizes[0].t.swizzle;
     }
-    if (best_ms) *best_ms = (best1 + best2) * 1e-3;
+    if (best_ms) *best_ms = iteration_ms;
     return STAG_OK;
 }
 

@@ -5,9 +5,12 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <set>
 #include <string>
 #include <thread>
 #include <vector>
+
+#include <unistd.h>
 
 #include <hip/hip_runtime.h>
 
@@ -368,6 +371,41 @@ static void resident_launches_are_short() {
     }
 }
 
+// stag_tune covers the kernels that the iterations run: groups of 8 and 4, not
+// only the whole block.
+static void tuned_sizes() {
+    char path[] = "/tmp/stag_tune_XXXXXX";
+    const int fd = mkstemp(path);
+    CHECK(fd >= 0);
+    setenv("STAG_TUNE_CACHE", path, 1);
+    const std::vector<std::pair<int, std::set<int>>> want = {
+        {1, {1}}, {4, {4}}, {6, {4, 8}}, {8, {4, 8}}, {11, {3, 8, 12}}, {12, {4, 8, 12}}, {16, {8, 16}}};
+    for (auto& w : want) {
+        CHECK(truncate(path, 0) == 0);
+        stag_ctx* c = nullptr;
+        CHECK(stag_create(0, 0, &c) == STAG_OK);
+        stag_gauge* g = make_gauge(c, k88, STAG_MASK_F64 | STAG_MASK_F32);
+        for (int again = 0; again < 2; ++again)
+            CHECK(stag_tune(c, g, STAG_F32, w.first, nullptr, nullptr) == STAG_OK);
+        int loaded = 0, measured = 0;
+        CHECK(stag_tune_counts(c, &loaded, &measured) == STAG_OK && loaded == 1 && measured == 1);
+        std::set<int> got;
+        FILE* f = fopen(path, "r");
+        char arch[64];
+        int pairs, r12, prec, n;
+        unsigned vh;
+        char rest[128];
+        while (f && fscanf(f, "%63s %d %d %u %d %d :%127[^\n]", arch, &pairs, &r12, &vh, &prec, &n, rest) == 7) got.insert(n);
+        if (f) fclose(f);
+        CHECK(got == w.second);
+        double us[3];
+        CHECK(stag_time_kernels(c, g, STAG_F32, w.first, 2, us) == STAG_OK);
+        stag_destroy(c);
+    }
+    close(fd);
+    unlink(path);
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
@@ -375,6 +413,7 @@ int main(int argc, char** argv) {
         {"budget", budget},
         {"failed_sync", failed_sync},
         {"temporaries", temporaries},
+        {"tuned_sizes", tuned_sizes},
         {"resident_gives_up", resident_gives_up},
         {"resident_together", resident_together},
         {"resident_launches_are_short", resident_launches_are_short},
