@@ -740,9 +740,12 @@ __global__ __launch_bounds__(kBlock) void k_hop1(HopArgs a) {
 // fp32 with Eq.5's four pairs keeps k_hop too: there k_hop1 gained 3 % on A with
 // full links at 32^3 x 64 (225 against 232 us), nothing with 12-parameter links
 // (160 us), and whole solves became slower (16^3 x 32 27.1 against 25.4 ms,
-// 24^3 x 48 full 136.5 against 134.7 ms).
-template <int P, int NP>
-constexpr bool kUseHop1 = P != P32 || NP == 8;
+// 24^3 x 48 full 136.5 against 134.7 ms). So do, of the improved operator's fp32
+// kernels, those of a solve: stage 2 with its product and stage 1 with the
+// deferred direction (20 x 18 x 22 x 30 33.5 against 40.5 ms a solve, 24^3 x 48 79.9
+// against 82.6).
+template <int P, int NP, int EPI, bool LAZY>
+constexpr bool kUseHop1 = P != P32 || (NP == 8 && EPI != EPI_XPAY_DOT && !LAZY);
 
 template <int P, int S, int EPI, bool R12, bool LAZY>
 static hipError_t run_hop1(const HopArgs& a, const Issue& is) {
@@ -757,14 +760,15 @@ static hipError_t run_hop1(const HopArgs& a, const Issue& is) {
 template <int P, int EPI>
 static hipError_t dispatch_hop1(const HopArgs& a, const Issue& is) {
     constexpr int S = HOP_NP / 4;
+    constexpr bool lazy = EPI != EPI_XPAY && kUseHop1<P, HOP_NP, EPI, true>;
     if constexpr (HOP_NP == 4) {
         if (a.r12) {
-            if constexpr (EPI != EPI_XPAY)
+            if constexpr (lazy)
                 if (a.lazy_r) return run_hop1<P, S, EPI, true, true>(a, is);
             return run_hop1<P, S, EPI, true, false>(a, is);
         }
     }
-    if constexpr (EPI != EPI_XPAY)
+    if constexpr (lazy)
         if (a.lazy_r) return run_hop1<P, S, EPI, false, true>(a, is);
     return run_hop1<P, S, EPI, false, false>(a, is);
 }
@@ -791,14 +795,10 @@ static hipError_t run_block(int S, const HopArgs& a, const Issue& is) {
 template <int P, int EPI>
 static hipError_t dispatch_epi(int S, int N, bool nt, const HopArgs& a, const Issue& is) {
     if (N == 1) {
-        if constexpr (EPI != EPI_RESID && kUseHop1<P, HOP_NP>) {
-            // fp32 solves of the improved operator: stage 2 and stage 1 with the
-            // deferred direction stay with k_hop (20 x 18 x 22 x 30 33.5 against
-            // 40.5 ms a solve, 24^3 x 48 79.9 against 82.6)
-            constexpr bool solve32 = P == P32 && EPI == EPI_XPAY_DOT;
-            if (nt && S == HOP_NP / 4 && !solve32 && !(P == P32 && a.lazy_r) && !a.lazy_y && !a.gate &&
-                a.g.Vh < kHop32MaxSites &&
-                !(EPI == EPI_XPAY && a.lazy_r) && !(a.fin.partials && (EPI != EPI_PLAIN || !a.lazy_r)))
+        if constexpr (EPI != EPI_RESID && kUseHop1<P, HOP_NP, EPI, false>) {
+            constexpr bool lazy = EPI != EPI_XPAY && kUseHop1<P, HOP_NP, EPI, true>;
+            if (nt && S == HOP_NP / 4 && (lazy || !a.lazy_r) && !a.lazy_y && !a.gate &&
+                a.g.Vh < kHop32MaxSites && !(a.fin.partials && (EPI != EPI_PLAIN || !a.lazy_r)))
                 return dispatch_hop1<P, EPI>(a, is);
         }
         if (nt) {
