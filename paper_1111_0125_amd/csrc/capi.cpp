@@ -525,23 +525,25 @@ int gauge_create(stag_ctx* ctx, const int L[4], const double* U, const double* U
     int* bad = nullptr;  // 12-parameter links: the third row is only rebuilt right for SU(3)
     int hbad = 0;
     hipStream_t s = ctx->stream;
+    // (links that STAG_GAUGE_R12 cannot take are refused as such also when there is
+    // no memory for their copies)
+    const bool check = r12 && (rc == STAG_OK || rc == STAG_ENOMEM);
+    constexpr double tol = 1e-10;
+    if (check) {
+        e = pool_malloc(ctx, (void**)&bad, sizeof(int), s);
+        if (e == hipSuccess) e = hipMemsetAsync(bad, 0, sizeof(int), s);
+    }
+    const bool pass = rc == STAG_OK && (g->G[P64][0] || g->G[P32][0]);
+    if (check && !pass && e == hipSuccess) e = launch_su3_check(Usrc, (uint64_t)V * 4, tol, bad, s);
     if (rc == STAG_OK) {
-        constexpr double tol = 1e-10;
-        const bool pass = g->G[P64][0] || g->G[P32][0];
-        if (r12) {
-            e = pool_malloc(ctx, (void**)&bad, sizeof(int), s);
-            if (e == hipSuccess) e = hipMemsetAsync(bad, 0, sizeof(int), s);
-            if (e == hipSuccess && !pass) e = launch_su3_check(Usrc, (uint64_t)V * 4, tol, bad, s);
-        }
         if (e == hipSuccess && pass)
             e = launch_gauge_scatter(Usrc, false, npairs, g->G[P64], g->G[P32], g->g, r12, tol, bad, s);
         if (e == hipSuccess && pass && Nsrc)
             e = launch_gauge_scatter(Nsrc, true, npairs, g->G[P64], g->G[P32], g->g, r12, tol, nullptr, s);
         for (int q = 0; q < 2 && e == hipSuccess && g->G[P16S][0]; ++q)
             e = launch_gauge_pack16(Usrc, Nsrc, g->G[P16S][q], g->gscale[q], g->g, q, r12, s);
-        if (e == hipSuccess && bad)
-            e = hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s);
     }
+    if (e == hipSuccess && bad) e = hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s);
     hipError_t e2 = hipStreamSynchronize(s);
     if (e == hipSuccess) e = e2;
     if (bad) (void)hipFreeAsync(bad, s);
@@ -550,7 +552,7 @@ int gauge_create(stag_ctx* ctx, const int L[4], const double* U, const double* U
         (void)hipGetLastError();
         rc = set_error(ctx, STAG_EDEVICE, "gauge pack: %s", hipGetErrorString(e));
     }
-    if (rc == STAG_OK && hbad)
+    if (e == hipSuccess && hbad)
         rc = set_error(ctx, STAG_EINVAL,
                        "stag_gauge_create: STAG_GAUGE_R12 needs SU(3) links "
                        "(|U U^+ - 1| or |det U - 1| above 1e-10)");

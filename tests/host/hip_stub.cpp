@@ -470,14 +470,14 @@ hipError_t launch_tiny_apply(int, int, const TinyApplyArgs&, hipStream_t s) {
 }
 
 hipError_t launch_gauge_scatter(const void*, bool, int, void* const*, void* const*, const Geom&, bool, double,
-                                int*, hipStream_t s) {
-    return issue(Issue{s}, [] {});
+                                int* bad, hipStream_t s) {
+    return issue(Issue{s}, [=] { if (bad && ctl.bad_links) *bad = 1; });
 }
 hipError_t launch_gauge_pack16(const void*, const void*, void*, float*, const Geom&, int, bool, hipStream_t s) {
     return issue(Issue{s}, [] {});
 }
-hipError_t launch_su3_check(const void*, uint64_t, double, int*, hipStream_t s) {
-    return issue(Issue{s}, [] {});
+hipError_t launch_su3_check(const void*, uint64_t, double, int* bad, hipStream_t s) {
+    return issue(Issue{s}, [=] { if (ctl.bad_links) *bad = 1; });
 }
 hipError_t launch_import(int prec, const void* src, void* dst, size_t rs, uint32_t Vh, int n, hipStream_t s) {
     return issue(Issue{s}, [=] {

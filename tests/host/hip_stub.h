@@ -20,6 +20,7 @@ struct Control {
     std::atomic<int> fail_device_sync{0};    // != 0: hipDeviceSynchronize fails without waiting
     std::atomic<size_t> memory_limit{0};     // device bytes that can be allocated; 0: no limit
     std::atomic<int> resident_gives_up{0};   // the resident kernel's waits run out
+    std::atomic<int> bad_links{0};           // the link check finds a link that is not SU(3)
     std::atomic<int> kernel_ms{0};           // how long a resident or operator kernel takes
     // what happened
     std::atomic<size_t> held{0};             // device bytes of hipMalloc and the pools

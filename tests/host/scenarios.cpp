@@ -406,6 +406,26 @@ static void tuned_sizes() {
     unlink(path);
 }
 
+// 12-parameter links that are not SU(3) are refused as that, with memory for the
+// copies or without, and leave nothing held; good ones without memory ENOMEM.
+static void bad_links() {
+    for (int mask : {STAG_MASK_F64, STAG_MASK_F16S, STAG_MASK_F64 | STAG_MASK_F32 | STAG_MASK_F16S})
+        for (size_t budget : {(size_t)0, (size_t)65536, (size_t)1 << 20})
+            for (int bad : {0, 1}) {
+                ctl.bad_links = bad;
+                stag_ctx* c = nullptr;
+                CHECK(stag_create(0, budget, &c) == STAG_OK);
+                std::vector<double> U(k88.vh() * 2 * 72, 0.0);
+                stag_gauge* g = nullptr;
+                const int rc = stag_gauge_create(c, k88.L, U.data(), 0, mask | STAG_GAUGE_R12, &g);
+                CHECK(rc == (bad ? STAG_EINVAL : budget == 0 || (mask == STAG_MASK_F16S && budget > 900000) ? STAG_OK : STAG_ENOMEM));
+                CHECK((g != nullptr) == (rc == STAG_OK));
+                stag_destroy(c);
+                CHECK(ctl.malloc_held == 0);
+            }
+    ctl.bad_links = 0;
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
@@ -414,6 +434,7 @@ int main(int argc, char** argv) {
         {"failed_sync", failed_sync},
         {"temporaries", temporaries},
         {"tuned_sizes", tuned_sizes},
+        {"bad_links", bad_links},
         {"resident_gives_up", resident_gives_up},
         {"resident_together", resident_together},
         {"resident_launches_are_short", resident_launches_are_short},
