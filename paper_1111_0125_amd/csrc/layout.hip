@@ -27,6 +27,11 @@ __device__ __forceinline__ char* pair_at(void* G, uint32_t s, int pr, int npairs
     return (char*)G + (size_t)(s / kLinkTile) * (kLinkTile * npairs * pb) + (size_t)pr * (kLinkTile * pb);
 }
 
+// A stored link has no NaN but the canonical one, of either sign: the resident
+// kernel marks empty words with another, which links in memory filled with ones
+// would pass on.
+__device__ __forceinline__ double plain_nan(double v) { return v == v ? v : __longlong_as_double(0x7ff8ll << 48); }
+
 // ------------------------------------------------------------------ fp64 and fp32 copies in one pass
 
 // Where one field of links goes: U (or the fat links) to pairs 0..3 over one
@@ -171,8 +176,8 @@ __global__ __launch_bounds__(kBlock) void k_gauge_scatter(ScatterArgs a) {
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
         const d2v v = u[e];
-        ur[e] = v.x;
-        ui[e] = v.y;
+        ur[e] = plain_nan(v.x);
+        ui[e] = plain_nan(v.y);
     }
     if constexpr (R12) {
         if (a.bad && !(su3_error(ur, ui) <= a.tol)) *a.bad = 1;
@@ -247,12 +252,12 @@ __device__ __forceinline__ void hop_pair(const d2v* __restrict__ U, const d2v* _
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const d2v f = uf[i * 3 + k];
-            lr[3 * i + k] = ef * f.x;
-            li[3 * i + k] = ef * f.y;
+            lr[3 * i + k] = ef * plain_nan(f.x);
+            li[3 * i + k] = ef * plain_nan(f.y);
             // -(eb W)^dagger: entry (i, k) = -eb conj(W[k][i])
             const d2v v = ub[k * 3 + i];
-            lr[9 + 3 * i + k] = -eb * v.x;
-            li[9 + 3 * i + k] = eb * v.y;
+            lr[9 + 3 * i + k] = -eb * plain_nan(v.x);
+            li[9 + 3 * i + k] = eb * plain_nan(v.y);
         }
 }
 

@@ -173,9 +173,10 @@ __device__ __forceinline__ double block_sum(double v, double* sv, double* sw) {
     return (sw[0] + sw[1]) + (sw[2] + sw[3]);
 }
 
-// What an empty word of t holds: a NaN that arithmetic does not produce. (A
-// right-hand side or link that carried it in would make the wait run out, and
-// the solve take a kernel per stage.)
+// What an empty word of t holds: a NaN that arithmetic does not produce. It could
+// only be passed on from an operand, and none has it: the vectors are finite
+// when a solve starts, and the stored links hold no NaN but the canonical one
+// (plain_nan in layout.hip).
 constexpr Word kEmpty = ~0ull;
 
 template <int P>

@@ -192,3 +192,26 @@ def test_small_solves_of_several_threads_share_the_device(stag):
         assert counts == (solves, 0)
         for x in xs:
             assert np.array_equal(x, got["alone", k][0][0])
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32", "f16s"])
+def test_links_of_all_ones_bytes_end_as_by_stages(stag, inner):
+    """Memory filled with ones is a NaN whose bits mark an empty word in the
+    resident kernel: the solve ends as with a kernel per stage (breakdown in fp64
+    and fp32), and no wait runs out."""
+    L = (8, 8, 4, 8)
+    U = links(L, "haar", 65).copy()
+    U.view(np.uint64)[...] = np.uint64(0xFFFFFFFFFFFFFFFF)
+    b = synth.gaussian_rhs(L, 1, 66)
+    with stag.Context(0) as c:
+        g = c.gauge(L, U, precisions=("f64", "f32", "f16s"))
+        fb, fx = c.field(g, 0, "f64", 1).load(b), c.field(g, 0, "f64", 1)
+        res = [stag.stag_cg_solve(c, g, [0.2], fb, fx, stag.cg_params(tol=1e-8, inner=inner, escalate=False,
+                                                                      max_iter=50, small_lattice=small))
+               for small in (True, False)]
+        (rc1, st1), (rc2, st2) = res
+        log("all ones", inner, res)
+        assert rc1 == rc2 and st1[0]["iters"] == st2[0]["iters"]
+        if inner != "f16s":
+            assert rc1 == stag.STAG_EBREAKDOWN
+        assert stag.stag_resident_counts(c) == (1, 0)
