@@ -266,7 +266,7 @@ typedef struct stag_cg_params {
                           kernel-per-stage solver (above 648 sites with use_graph
                           only). Such solves of one process share a device as long
                           as their workgroups (one per 64 to 256 sites and
-                          right-hand side) number 32 together; one that has no
+                          right-hand side) number 28 together; one that has no
                           room beside the others takes the kernel-per-stage
                           solver, as does every solve of a context after the
                           waits inside such a kernel ran out once
@@ -318,7 +318,7 @@ int stag_cg_solve(stag_ctx* ctx, const stag_gauge* gauge, const double* mass,
 /* Resident kernels of small lattices (small_lattice above): their workgroups
  * wait for each other inside the kernel, which needs all of them on the
  * device; kernels of other streams that find no free compute unit wait for the
- * end of a launch (on 16^4 and 16^3 x 32 about 0.5 ms). A wait that runs out (2 s; another process on the device can hold
+ * end of a launch (0.3 to 0.6 ms). A wait that runs out (2 s; another process on the device can hold
  * compute units) ends the kernel; the solve starts over with a kernel per
  * stage, and so does every later one of the context.
  * stag_resident_wait: sets the longest such wait in seconds (< 0: every wait

@@ -775,13 +775,15 @@ static int launch_block_graphs(EngineRun& R, int busy, int K) {
 // ------------------------------------------------------------------ resident iterations
 
 // Iterations per launch of the resident kernel. A launch keeps its compute units
-// to itself (10 to 16 us an iteration); with most of the device's in use,
-// kernels of other streams wait for its end, so there it is kept short. A
-// 4^4 operator call with its copy back beside 16^4 plain CG / 16^3 x 32 fp32
-// solves (median, and the solve alone): 64 iterations a launch 0.51 / 0.29 ms
-// (51.8 / 33.6 ms), 128 1.5 / 1.1 (51.2 / 33.3), 256 3.6 / 2.8 (50.8 / 33.4), 1024
-// 16.1 / 3.4 (50.7 / 33.2; in mixed CG the updates end a launch before); with a
-// kernel per stage 0.07 (82.5 / 55.3).
+// to itself (10 to 16 us an iteration). Workgroups of other streams' kernels go
+// to the XCDs in turn and wait where all units are in use, so a launch that
+// holds more than 7/8 of any XCD's is kept short. An operator call on 4^4 (one
+// workgroup) / 8^4 with its copy back, median ms, beside solves (their own
+// time), with 1024, 64 iterations a launch and with a kernel per stage: 16^4 fp64
+// 16.0 / 16.0 (50.6), 0.50 / 0.53 (51.7), 0.07 / 0.12 (80.8); 16^3 x 32 fp32 3.5 / 3.5
+// (33.1), 0.30 / 0.31 (33.9), 0.07 / 0.09 (55.6; in mixed CG the updates end launches
+// too); 8^3 x 16 fp64 with all of one XCD 0.06 / 14.7 (15.3), 0.06 / 0.61 (15.6), 0.07
+// / 0.08 (22.6); with 3/4 of each XCD 0.06 / 0.09 either way (15.4 and 15.8).
 constexpr int kPersistIters = 1024;
 constexpr int kPersistItersWide = 64;
 // Rounds (one launch and its fix-up) between polls.
@@ -790,8 +792,9 @@ constexpr int kPersistRounds = 3;
 // The compute units that resident kernels hold, per device and process. Two of
 // them that are each only partly on the device would wait for each other, so
 // one is let in beside others only when all their workgroups together, at one
-// per compute unit, fit on any single XCD (32 units): then each is wholly
-// resident wherever its workgroups land. A larger one runs alone.
+// per compute unit, fit on any single XCD (32 units; 7/8 of them, which leaves
+// room for other kernels): then each is wholly resident wherever its workgroups
+// land. A larger one runs alone.
 struct ResidentUnits {
     std::mutex mu;
     int used = 0;
@@ -807,7 +810,7 @@ struct ResidentHold {
     ~ResidentHold() { release(); }
     bool take(int blocks, int cus) {
         std::lock_guard<std::mutex> lk(u.mu);
-        if (u.used != 0 && u.used + blocks > cus / 8) return false;
+        if (u.used != 0 && u.used + blocks > cus / 8 - cus / 64) return false;
         u.used += held = blocks;
         return true;
     }
@@ -864,7 +867,8 @@ static int enqueue_persist_rounds(EngineRun& R, int nk) {
     a.nrhs = R.nrhs;
     a.blocks = (int)hop_blocks(e->Vh, R.persist);
     a.one_xcd = a.blocks * ((R.nrhs + 7) / 8) <= 32;
-    a.max_iters = 2 * a.blocks * a.nrhs > e->ctx->cus ? kPersistItersWide : kPersistIters;
+    const int per_xcd = a.one_xcd ? a.blocks * ((R.nrhs + 7) / 8) : (a.blocks * a.nrhs + 7) / 8;
+    a.max_iters = 8 * per_xcd > e->ctx->cus - e->ctx->cus / 8 ? kPersistItersWide : kPersistIters;
     a.limit = e->ctx->resident_wait;
     Ctx c{e, Issue{R.s}, nk, false, R.variant};
     for (int k = 0; k < kPersistRounds; ++k) {

@@ -321,8 +321,8 @@ static void resident_gives_up() {
 }
 
 // Solves of several threads at once, each with a context of its own: small ones
-// run in resident kernels beside each other, never with more workgroups than one
-// XCD has units; a large one runs alone or with a kernel per stage.
+// run in resident kernels beside each other, never with more workgroups than 7/8
+// of one XCD's units; a large one runs alone or with a kernel per stage.
 static void resident_together() {
     ctl.kernel_ms = 20;
     auto run = [](const Lattice& l, int threads, int64_t* resident) {
@@ -346,27 +346,35 @@ static void resident_together() {
     };
     int64_t n = 0;
     run(k44, 6, &n);  // 2 workgroups each
-    CHECK(n == 18 && ctl.persist_most >= 2 && ctl.blocks_most <= 32);
+    CHECK(n == 18 && ctl.persist_most >= 2 && ctl.blocks_most <= 28);
     ctl.persist_most = ctl.blocks_most = 0;
     run(k66, 6, &n);  // 11 each: two at a time
-    CHECK(n >= 3 && ctl.persist_most <= 2 && ctl.blocks_most <= 32);
+    CHECK(n >= 3 && ctl.persist_most <= 2 && ctl.blocks_most <= 28);
     ctl.persist_most = ctl.blocks_most = 0;
     run(k16, 3, &n);  // 256: alone
     CHECK(n >= 1 && ctl.persist_most == 1);
     ctl.kernel_ms = 0;
 }
 
-// A resident kernel that holds most of the compute units leaves them after a
-// bounded number of iterations.
+// A resident kernel that holds more than 7/8 of an XCD's compute units (in fp32
+// 128 sites a workgroup; up to 32 of them on one XCD, more over all) leaves them
+// after a bounded number of iterations.
 static void resident_launches_are_short() {
-    for (const Lattice& l : {k16, Lattice{{16, 16, 16, 32}}, k88}) {
+    const struct {
+        Lattice l;
+        int n;
+        bool is_short;
+    } cases[] = {{k16, 1, true},  {{{16, 16, 16, 32}}, 1, true}, {{{8, 8, 8, 16}}, 1, true},
+                 {k88, 16, true}, {{{8, 8, 8, 12}}, 1, false},   {k88, 8, false}};
+    for (auto& k : cases) {
         stag_ctx* c = nullptr;
         CHECK(stag_create(0, 0, &c) == STAG_OK);
-        stag_gauge* g = make_gauge(c, l, STAG_MASK_F64 | STAG_MASK_F32);
+        stag_gauge* g = make_gauge(c, k.l, STAG_MASK_F64 | STAG_MASK_F32);
         ctl.persist_iters = 0;
         Solve s;
+        s.n = k.n;
         CHECK(solve(c, g, s) == STAG_OK);
-        CHECK(ctl.persist_iters > 0 && (l.vh() <= 16384 || ctl.persist_iters <= 64));
+        CHECK(ctl.persist_iters > 0 && (ctl.persist_iters <= 64) == k.is_short);
         stag_destroy(c);
     }
 }
