@@ -41,6 +41,7 @@ UNITS = [
     ("tiny.hip", "tiny.o", []),
     ("persist.hip", "persist.o", []),
     ("scratch.hip", "scratch.o", []),
+    ("streams.hip", "streams.o", []),
     ("capi.cpp", "capi.o", []),
     ("solver.cpp", "solver.o", []),
     ("serve.cpp", "serve.o", []),

@@ -416,6 +416,7 @@ int stag_destroy(stag_ctx* ctx) {
         gauges.swap(ctx->gauges);
     }
     for (auto* e : engines) engine_destroy(e);
+    branches_destroy(ctx);
     for (auto* f : fields) {
         dev_free(ctx, f->data, f->rs * f->nrhs);
         delete f;

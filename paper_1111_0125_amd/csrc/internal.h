@@ -67,6 +67,12 @@ struct stag_ctx {
     mutable std::mutex kept_mu;
     size_t budget = 0;             // covers used and kept_bytes together
     std::atomic<size_t> used{0};   // by the context's objects
+    // Sets of streams that run side by side, for the groups of block solves
+    // (take_branches), and what finding them needs.
+    std::vector<std::vector<hipStream_t>> branch_sets;
+    std::mutex branch_mu;
+    int* meet = nullptr;
+    int meet_token = 0;
     std::mutex mu;                 // guards the object lists and the workspace pool
     std::string err;
     std::mutex err_mu;
@@ -150,7 +156,7 @@ struct stag_engine {
         hipStream_t s = nullptr;
         hipEvent_t done = nullptr;
     };
-    std::vector<Branch> gstreams;   // one per group of a block of several
+    std::vector<Branch> gstreams;   // for the groups of a block, a set of the context's
     hipEvent_t gfork = nullptr;
     stag::HopTune tune_lo, tune_64;
 };
@@ -223,6 +229,8 @@ int set_error(stag_ctx* ctx, int code, const char* fmt, ...);
 // device and kept).
 constexpr size_t kScratchBytes = (size_t)48 << 20;
 hipError_t scratch_init(int device, void** out);
+hipError_t streams_meet(hipStream_t a, hipStream_t b, int* dev, int token, bool* apart);
+void branches_destroy(stag_ctx* ctx);
 int dev_alloc(stag_ctx* ctx, size_t bytes, void** p);
 void dev_free(stag_ctx* ctx, void* p, size_t bytes);
 int kept_alloc(stag_ctx* ctx, size_t bytes, void** p);

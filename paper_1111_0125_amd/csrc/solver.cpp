@@ -62,9 +62,14 @@ void engine_destroy(stag_engine* e) {
         if (e->ev[i]) (void)hipEventDestroy(e->ev[i]);
     }
     if (e->hstage) (void)hipHostFree(e->hstage);
+    std::vector<hipStream_t> set;
     for (auto& br : e->gstreams) {
         if (br.done) (void)hipEventDestroy(br.done);
-        (void)hipStreamDestroy(br.s);
+        set.push_back(br.s);
+    }
+    if (!set.empty()) {
+        std::lock_guard<std::mutex> lk(ctx->branch_mu);
+        ctx->branch_sets.push_back(set);
     }
     if (e->gfork) (void)hipEventDestroy(e->gfork);
     ctx->used.fetch_sub(e->bytes);
@@ -722,26 +727,81 @@ static int get_graph(EngineRun& R, int g0, int nk, int K, hipGraphExec_t* out) {
     return STAG_OK;
 }
 
+// Streams on different hardware queues for the groups of a block: at most three
+// (8 + 4 + 1 of 13 right-hand sides). Sets are kept in the context; a new one costs
+// two to ten streams' creation and under 0.1 ms for each pair that is tried (0.3
+// for one on the same queue).
+constexpr int kBranches = 3;
+constexpr int kBranchTries = 8;
+
+static int take_branches(stag_engine* e, std::vector<hipStream_t>& set) {
+    stag_ctx* ctx = e->ctx;
+    std::lock_guard<std::mutex> lk(ctx->branch_mu);
+    if (!ctx->branch_sets.empty()) {
+        set = ctx->branch_sets.back();
+        ctx->branch_sets.pop_back();
+        return STAG_OK;
+    }
+    hipError_t err = hipSuccess;
+    if (!ctx->meet) {
+        err = hipMalloc((void**)&ctx->meet, 4 * sizeof(int));
+        if (err == hipSuccess) err = hipMemsetAsync(ctx->meet, 0, 4 * sizeof(int), ctx->stream);
+        if (err == hipSuccess) err = hipStreamSynchronize(ctx->stream);
+    }
+    std::vector<hipStream_t> spare;
+    for (int k = 0; k < kBranchTries && (int)set.size() < kBranches && err == hipSuccess; ++k) {
+        hipStream_t s = nullptr;
+        if ((err = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess) break;
+        bool apart = true;
+        for (hipStream_t q : set)
+            if (apart && err == hipSuccess) err = streams_meet(q, s, ctx->meet, ++ctx->meet_token, &apart);
+        (apart && err == hipSuccess ? set : spare).push_back(s);
+    }
+    // none found for a place (a device with other work): any stream serves
+    while ((int)set.size() < kBranches && !spare.empty() && err == hipSuccess) {
+        set.push_back(spare.back());
+        spare.pop_back();
+    }
+    if (err != hipSuccess) spare.insert(spare.end(), set.begin(), set.end());
+    for (hipStream_t s : spare) (void)hipStreamDestroy(s);
+    if (err == hipSuccess) return STAG_OK;
+    set.clear();
+    (void)hipGetLastError();
+    return set_error(ctx, STAG_EDEVICE, "solver: streams of a block's groups: %s", hipGetErrorString(err));
+}
+
+void branches_destroy(stag_ctx* ctx) {
+    for (auto& set : ctx->branch_sets)
+        for (hipStream_t s : set) (void)hipStreamDestroy(s);
+    ctx->branch_sets.clear();
+    (void)hipFree(ctx->meet);
+    ctx->meet = nullptr;
+}
+
 // One block as graphs: a single group's on the run's stream; several groups'
 // each on a stream of the engine that starts after the run's stream and is
-// waited for by it, so the groups overlap on the device. The engine's streams
-// are created together, which gives them different hardware queues; the
-// run's stream may share one with any of them (5 RHS on 16^3 x 32, the first
-// group on the run's stream: 42 or 56 ms per solve, depending on what else had
-// created streams before).
+// waited for by it, so the groups overlap on the device. Two streams of one
+// hardware queue do not (us per iteration, 12-parameter links, 16^3 x 32 fp32, 8 RHS
+// 98.0 against 71.4, 5 RHS 83.4 and 59.6), and which queue a stream gets depends on
+// what else the program has created: streams that do are looked for.
 static int launch_block_graphs(EngineRun& R, int busy, int K) {
     stag_engine* e = R.e;
     const std::vector<Group> groups = slot_groups(e->Vh, busy);
     const int n = (int)groups.size();
-    if (n > 1 && (int)e->gstreams.size() < n) {
-        if (!e->gfork) RCK(hipEventCreateWithFlags(&e->gfork, hipEventDisableTiming));
-        const size_t want = std::max((size_t)n, slot_groups(e->Vh, e->N).size());
-        while (e->gstreams.size() < want) {
-            stag_engine::Branch br;
-            RCK(hipStreamCreateWithFlags(&br.s, hipStreamNonBlocking));
-            e->gstreams.push_back(br);
-            RCK(hipEventCreateWithFlags(&e->gstreams.back().done, hipEventDisableTiming));
+    if (n > kBranches) return set_error(e->ctx, STAG_EINVAL, "solver: %d groups", n);
+    if (n > 1 && e->gstreams.empty()) {
+        std::vector<hipStream_t> set;
+        int rc = take_branches(e, set);
+        if (rc) return rc;
+        for (hipStream_t s : set) {
+            e->gstreams.emplace_back();
+            e->gstreams.back().s = s;
         }
+    }
+    if (n > 1) {
+        if (!e->gfork) RCK(hipEventCreateWithFlags(&e->gfork, hipEventDisableTiming));
+        for (auto& br : e->gstreams)
+            if (!br.done) RCK(hipEventCreateWithFlags(&br.done, hipEventDisableTiming));
     }
     if (n > 1) RCK(hipEventRecord(e->gfork, R.s));
     auto launch = [&](int i) -> int {

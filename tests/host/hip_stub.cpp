@@ -40,6 +40,7 @@ struct Stream {
     std::condition_variable cv;
     std::deque<Op> work, done;
     long submitted = 0, executed = 0, retired = 0;
+    int queue = 0;
     bool dead = false;
 
     Stream() {
@@ -257,6 +258,8 @@ hipError_t hipDeviceSynchronize() {
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
     std::lock_guard<std::recursive_mutex> lk(g_mu);
     Stream* st = new Stream();
+    static int count = 0;
+    st->queue = ctl.paired_queues ? (count++ / 2) % 4 : count++ % 4;
     g_streams.push_back(st);
     *s = (hipStream_t)st;
     return hipSuccess;
@@ -371,6 +374,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t s) {
     Exec* x = (Exec*)e;
     if (x->dead) violation("a destroyed graph is launched");
     if (ctl.fail_graph_launch > 0 && --ctl.fail_graph_launch == 0) return hipErrorUnknown;
+    ctl.queues_used |= 1u << stream_of(s)->queue;
     x->pending += 1;
     stream_of(s)->push({[x] { for (auto& f : x->nodes) f(); }, [x] { x->pending -= 1; }, 20});
     return hipSuccess;
@@ -467,6 +471,11 @@ hipError_t launch_tiny(int, int n, const TinyArgs& a, hipStream_t s) {
 
 hipError_t launch_tiny_apply(int, int, const TinyApplyArgs&, hipStream_t s) {
     return issue(Issue{s}, [] { nap(ctl.kernel_ms); });
+}
+
+hipError_t streams_meet(hipStream_t a, hipStream_t b, int*, int, bool* apart) {
+    *apart = stream_of(a)->queue != stream_of(b)->queue;
+    return hipSuccess;
 }
 
 hipError_t launch_gauge_scatter(const void*, bool, int, void* const*, void* const*, const Geom&, bool, double,

@@ -28,6 +28,8 @@ struct Control {
     std::atomic<int> persist{0}, tiny{0}, stage{0};  // launches: resident, one workgroup, per stage
     std::atomic<int> persist_now{0}, persist_most{0};  // resident kernels running, and the most
     std::atomic<int> blocks_now{0}, blocks_most{0};  // their workgroups at one time
+    std::atomic<int> paired_queues{0};       // streams 0 and 1, 2 and 3, ... share a hardware queue of four
+    std::atomic<unsigned> queues_used{0};    // by graph launches, a bit each
     std::atomic<int> persist_iters{0};               // the most iterations given to one launch
 };
 extern Control ctl;

@@ -434,6 +434,31 @@ static void bad_links() {
     ctl.bad_links = 0;
 }
 
+// The groups of a block run on streams of different hardware queues, whatever
+// streams the program created before.
+static void groups_on_queues_of_their_own() {
+    ctl.paired_queues = 1;
+    for (int before = 0; before < 4; ++before)
+        for (int n : {5, 8, 11, 13, 16}) {
+            hipStream_t other = nullptr;
+            for (int k = 0; k < before; ++k) (void)hipStreamCreateWithFlags(&other, 0);
+            stag_ctx* c = nullptr;
+            CHECK(stag_create(0, 0, &c) == STAG_OK);
+            for (int gauge = 0; gauge < 2; ++gauge) {
+                stag_gauge* g = make_gauge(c, k88, STAG_MASK_F64 | STAG_MASK_F32);
+                ctl.queues_used = 0;
+                Solve s;
+                s.n = n;
+                s.small = 0;
+                CHECK(solve(c, g, s) == STAG_OK);
+                CHECK(__builtin_popcount(ctl.queues_used) == (n == 13 ? 3 : 2));
+                CHECK(stag_gauge_destroy(g) == STAG_OK);
+            }
+            stag_destroy(c);
+            CHECK(ctl.malloc_held == 0);
+        }
+}
+
 int main(int argc, char** argv) {
     static const std::map<std::string, std::function<void()>> all = {
         {"lifetime", lifetime},
@@ -443,6 +468,7 @@ int main(int argc, char** argv) {
         {"temporaries", temporaries},
         {"tuned_sizes", tuned_sizes},
         {"bad_links", bad_links},
+        {"groups_on_queues_of_their_own", groups_on_queues_of_their_own},
         {"resident_gives_up", resident_gives_up},
         {"resident_together", resident_together},
         {"resident_launches_are_short", resident_launches_are_short},

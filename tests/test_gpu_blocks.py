@@ -2,13 +2,19 @@
 right-hand side the bits of a call of its own (the default launch shape's fast
 loop of 2 to 8 right-hand sides, and how larger calls are cut up)."""
 
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
 import synth
-from tests.gpu_common import links, oracle_apply_A
+from tests.gpu_common import links, log, oracle_apply_A
 
 pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(scope="module")
@@ -104,3 +110,36 @@ def test_blocks_of_twelve_equal_singles(stag, ctx, n, form):
         assert np.array_equal(o1.store()[0], got[k]), k
     for o in (fi, fo, f1, o1, g):
         o.destroy()
+
+
+GROUPS = """
+import sys
+import torch
+stream = torch.cuda.Stream() if sys.argv[1] == "torch" else None
+import paper_1111_0125_amd as stag, synth
+L = (16, 16, 16, 32)
+with stag.Context(0) as ctx:
+    g = ctx.gauge(L, synth.exp_ih_links(L, 89, 0.3), precisions=("f64", "f32"), r12=True)
+    p = stag.cg_params(tol=1e-8, inner="f32", small_lattice=False)
+    t = {}
+    for n in (4, 8):
+        fb = ctx.field(g, 0, "f64", n).load(synth.gaussian_rhs(L, n, 90))
+        fx = ctx.field(g, 0, "f64", n)
+        runs = [stag.stag_cg_solve(ctx, g, [0.2] * n, fb, fx, p, stream=stream) for _ in range(6)]
+        assert all(rc == 0 for rc, st in runs)
+        t[n] = min(st[0]["seconds"] for rc, st in runs)
+print("RATIO", t[8] / t[4])
+"""
+
+
+@pytest.mark.parametrize("stream", ["torch", "own"])
+def test_groups_overlap_whatever_else_uses_streams(stream):
+    """8 right-hand sides on 16^3 x 32 run as two groups of 4 that overlap on the
+    device (1.5 times the time of one group) in a program that creates streams of
+    its own too; one after the other, as on streams that share a hardware queue,
+    they take 2.1 times. (A program of its own: torch comes with its HIP runtime.)"""
+    r = subprocess.run([sys.executable, "-c", GROUPS, stream], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr
+    ratio = float(r.stdout.split("RATIO")[1])
+    log("groups, solves on stream:", stream, ratio)
+    assert ratio < 1.85

@@ -42,7 +42,7 @@ def scenarios(tmp_path_factory):
 @pytest.mark.parametrize("name", ["lifetime", "launch_error", "small_without_graphs", "small_same_for_blocks",
                                   "budget", "failed_sync", "temporaries", "resident_gives_up",
                                   "resident_together", "resident_launches_are_short", "tuned_sizes",
-                                  "bad_links"])
+                                  "bad_links", "groups_on_queues_of_their_own"])
 def test_host_scenario(scenarios, name):
     env = {k: v for k, v in os.environ.items() if k != "STAG_TUNE_CACHE"}
     r = subprocess.run([scenarios, name], capture_output=True, text=True, timeout=120, env=env)
