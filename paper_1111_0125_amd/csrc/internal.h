@@ -265,7 +265,7 @@ void engine_release(stag_engine* e);
 struct Group {
     int g0, n;
 };
-std::vector<Group> slot_groups(uint32_t Vh, int busy);
+std::vector<Group> slot_groups(const stag_gauge* g, int prec, int busy);
 // Whether the iteration kernels of e (nk right-hand sides per kernel)
 // finalise reductions at their start (small lattices) or leave it to a
 // one-block kernel (large ones).

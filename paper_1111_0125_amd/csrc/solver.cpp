@@ -210,15 +210,26 @@ constexpr uint32_t kXpayMinSites = 131072;
 constexpr int kXpayMinRhs = 8;
 
 // Kernels serve groups of 8, 4, 3, 2 or 1 slots, each group its own chain, so
-// that no kernel has idle slots (its fast loop needs every one active) and none
-// more than 8 (per right-hand side an iteration costs less with 8 per kernel
-// than with 12 or 16, whose neighbour gathers miss the caches more). Below
-// kXpayMinSites sites per parity 5 to 8 slots run as two groups of 4, which
-// overlap (ms per solve, 16^3 x 32: 8 RHS 48.6 against 52.3 as one group, 5 RHS 42.2
-// against 51.3 as 4 + 1; on 24^3 x 48 8 RHS 415 against 350). 12 RHS as 8 + 4: 68.5
-// against 82.8 as three groups on 16^3 x 32, 501 against 506 on 24^3 x 48.
-std::vector<Group> slot_groups(uint32_t Vh, int busy) {
-    if (busy > 4 && busy <= 8 && Vh < kXpayMinSites) return {{0, 4}, {4, 4}};
+// that no kernel has more than 8 (per right-hand side an iteration costs less with
+// 8 per kernel than with 12 or 16, whose neighbour gathers miss the caches more)
+// and few idle slots (the fast loop needs every one active). Groups overlap on
+// the device (launch_block_graphs), which pays while one kernel leaves room:
+// below kXpayMinSites sites per parity 5 to 8 slots run as two groups of 4 (16^3 x 32
+// fp32, 12-parameter links, us per iteration: 8 RHS 69 against 74 as one group; on
+// 24^3 x 48 415 against 350 ms a solve), with the rest in a kernel of its own size
+// in fp16 (5 / 7 RHS 20 x 18 x 22 x 30 88 / 101 against 95 / 108 with idle slots; in fp32
+// 94.5 / 106.4 and 93.6 / 106.7, improved 65536 sites 112 / 119 and 107 / 117). 9 to 12 as
+// three groups below sites that halve with fp64 and with the improved operator's
+// links (12 RHS, three groups against 8 + 4: fp32 4096 sites 41.5 and 55.0, 32768 62.9
+// and 74.9, 65536 95.3 and 95.4, 118800 160.5 and 158.9; fp16 65536 87.4 and 92.1; fp64
+// 32768 90.0 and 91.9, 65536 155.9 and 147.9; improved fp32 32768 95.0 and 97.8, 65536
+// 177.5 and 166.4, fp64 13824 85.6 and 90.1, 32768 150.6 and 142.2).
+constexpr uint32_t kThreeGroupsSites = 131072;
+std::vector<Group> slot_groups(const stag_gauge* g, int prec, int busy) {
+    const uint32_t Vh = g->g.Vh;
+    if (busy > 4 && busy <= 8 && Vh < kXpayMinSites) return {{0, 4}, {4, prec == P16S ? busy - 4 : 4}};
+    const uint32_t three = kThreeGroupsSites / (g->npairs == 8 ? 2 : 1) / (prec == P64 ? 2 : 1);
+    if (busy > 8 && busy <= 12 && Vh < three) return {{0, 4}, {4, 4}, {8, busy - 8}};
     std::vector<Group> v;
     for (int g0 = 0; g0 < busy; g0 += v.back().n) v.push_back({g0, fit_n(busy - g0)});
     return v;
@@ -575,7 +586,7 @@ hipError_t enqueue_slots(const Ctx& c, int g0, int nk, int K, int F) {
 // One block for the slots below busy, group after group.
 hipError_t enqueue_block(const Ctx& c, int busy, int K, int F) {
     hipError_t err = hipSuccess;
-    for (const Group& g : slot_groups(c.e->Vh, busy))
+    for (const Group& g : slot_groups(c.e->gauge, c.e->prec, busy))
         if (err == hipSuccess) err = enqueue_slots(c, g.g0, g.n, K, F);
     return err;
 }
@@ -786,7 +797,7 @@ void branches_destroy(stag_ctx* ctx) {
 // what else the program has created: streams that do are looked for.
 static int launch_block_graphs(EngineRun& R, int busy, int K) {
     stag_engine* e = R.e;
-    const std::vector<Group> groups = slot_groups(e->Vh, busy);
+    const std::vector<Group> groups = slot_groups(e->gauge, e->prec, busy);
     const int n = (int)groups.size();
     if (n > kBranches) return set_error(e->ctx, STAG_EINVAL, "solver: %d groups", n);
     if (n > 1 && e->gstreams.empty()) {
@@ -1405,7 +1416,7 @@ extern "C" int stag_time_kernels(stag_ctx* ctx, const stag_gauge* g, int prec, i
     DeviceGuard dg(ctx->device);
     // the groups of an iteration one after the other (in a solve they overlap)
     double sum[3] = {0.0, 0.0, 0.0};
-    for (const Group& q : slot_groups(g->g.Vh, nrhs)) {
+    for (const Group& q : slot_groups(g, prec, nrhs)) {
         stag_engine* e = nullptr;
         int rc = engine_acquire(ctx, g, prec, q.n, &e);
         if (rc) return rc;

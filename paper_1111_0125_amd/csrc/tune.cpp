@@ -342,7 +342,7 @@ int stag_tune(stag_ctx* ctx, const stag_gauge* g, int prec, int nrhs, stag_tune_
         return STAG_OK;
     };
     int rc = STAG_OK;
-    for (const Group& q : slot_groups(g->g.Vh, nrhs))
+    for (const Group& q : slot_groups(g, prec, nrhs))
         if (rc == STAG_OK) rc = add(q.n, std::min(q.n, nrhs - q.g0));
     const double iteration_ms = ms;
     if (rc == STAG_OK && sizes[0].N != pick_n(nrhs)) rc = add(pick_n(nrhs), nrhs);
