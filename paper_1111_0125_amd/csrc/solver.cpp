@@ -213,23 +213,26 @@ constexpr int kXpayMinRhs = 8;
 // that no kernel has more than 8 (per right-hand side an iteration costs less with
 // 8 per kernel than with 12 or 16, whose neighbour gathers miss the caches more)
 // and few idle slots (the fast loop needs every one active). Groups overlap on
-// the device (launch_block_graphs), which pays while one kernel leaves room:
-// below kXpayMinSites sites per parity 5 to 8 slots run as two groups of 4 (16^3 x 32
-// fp32, 12-parameter links, us per iteration: 8 RHS 69 against 74 as one group; on
-// 24^3 x 48 415 against 350 ms a solve), with the rest in a kernel of its own size
-// in fp16 (5 / 7 RHS 20 x 18 x 22 x 30 88 / 101 against 95 / 108 with idle slots; in fp32
-// 94.5 / 106.4 and 93.6 / 106.7, improved 65536 sites 112 / 119 and 107 / 117). 9 to 12 as
-// three groups below sites that halve with fp64 and with the improved operator's
-// links (12 RHS, three groups against 8 + 4: fp32 4096 sites 41.5 and 55.0, 32768 62.9
-// and 74.9, 65536 95.3 and 95.4, 118800 160.5 and 158.9; fp16 65536 87.4 and 92.1; fp64
-// 32768 90.0 and 91.9, 65536 155.9 and 147.9; improved fp32 32768 95.0 and 97.8, 65536
-// 177.5 and 166.4, fp64 13824 85.6 and 90.1, 32768 150.6 and 142.2).
-constexpr uint32_t kThreeGroupsSites = 131072;
+// the device (launch_block_graphs), and groups of 4 that do are faster than one of 8
+// up to sizes where a single kernel fills it: the fewer bytes a site has the
+// later. us per iteration, 12-parameter links, groups of 4 against 8 (+ 4):
+//   8 RHS   fp32 65536 sites 69 and 74, 160000 149 and 157, 331776 277 and 282,
+//           526848 461 and 456; fp16 160000 131 and 148, 526848 344 and 376; fp64
+//           160000 258 and 257, 276480 439 and 442, 331776 557 and 540
+//   12 RHS  fp32 4096 41 and 55, 32768 63 and 75, 160000 198 and 208, 276480 336 and
+//           339, 331776 412 and 410; fp16 65536 87 and 92, 276480 266 and 291, 526848
+//           523 and 532; fp64 32768 90 and 92, 65536 156 and 148
+// improved operator: 8 RHS fp32 276480 sites 427 (branches of one graph) and 387; 12
+// RHS fp32 32768 95 and 98, 65536 178 and 166, fp16 32768 81 and 90, 65536 141 and 134,
+// fp64 13824 86 and 90, 32768 151 and 142. The rest of 5 to 7 gets a kernel of its
+// size in fp16 (5 / 7 RHS 118800 sites 88 / 101 against 95 / 108 with idle slots;
+// in fp32 94.5 / 106.4 and 93.6 / 106.7, improved 65536 sites 112 / 119 and 107 / 117).
 std::vector<Group> slot_groups(const stag_gauge* g, int prec, int busy) {
-    const uint32_t Vh = g->g.Vh;
-    if (busy > 4 && busy <= 8 && Vh < kXpayMinSites) return {{0, 4}, {4, prec == P16S ? busy - 4 : 4}};
-    const uint32_t three = kThreeGroupsSites / (g->npairs == 8 ? 2 : 1) / (prec == P64 ? 2 : 1);
-    if (busy > 8 && busy <= 12 && Vh < three) return {{0, 4}, {4, 4}, {8, busy - 8}};
+    const bool improved = g->npairs == 8;
+    const uint32_t two = improved || prec == P64 ? 131072 : prec == P32 ? 393216 : 786432;
+    const uint32_t three = improved && prec == P64 ? two / 4 : two / 2;
+    if (busy > 4 && busy <= 8 && g->g.Vh < two) return {{0, 4}, {4, prec == P16S ? busy - 4 : 4}};
+    if (busy > 8 && busy <= 12 && g->g.Vh < three) return {{0, 4}, {4, 4}, {8, busy - 8}};
     std::vector<Group> v;
     for (int g0 = 0; g0 < busy; g0 += v.back().n) v.push_back({g0, fit_n(busy - g0)});
     return v;
