@@ -70,14 +70,20 @@ def csrc_digest():
     return h.hexdigest()
 
 
-def kernel_names(tune, inner, npairs=4):
-    """Symbol names of the three iteration kernels for a tuned shape (one RHS)."""
+def kernel_names(tune, inner, r12):
+    """Symbol names of the three iteration kernels for a tuned shape on 16^3x32 (one
+    RHS): fp64 and fp16 stages in the default shape are k_hop1, fp32's k_hop."""
     p = {"f64": 0, "f32": 1, "f16s": 2}[inner]
     nt = "true" if tune["nt"] else "false"
     op = 2 if inner == "f64" else 3
-    return [f"void stag::k_hop<{p}, {tune['S1']}, 1, 0, {nt}, {npairs}>(stag::HopArgs)",
-            f"void stag::k_hop<{p}, {tune['S2']}, 1, 2, {nt}, {npairs}>(stag::HopArgs)",
-            f"void stag::k_vec<{p}, 1, {op}>(stag::VecArgs)"]
+
+    def hop(S, epi):
+        if inner != "f32" and tune["nt"] and S == 1:
+            return (f"void stag::k_hop1<{p}, 1, {epi}, 4, {'true' if r12 else 'false'}, true, "
+                    f"{'true' if epi == 0 else 'false'}>(stag::HopArgs)")
+        return f"void stag::k_hop<{p}, {S}, 1, {epi}, {nt}, 4>(stag::HopArgs)"
+
+    return [hop(tune["S1"], 0), hop(tune["S2"], 2), f"void stag::k_vec<{p}, 1, {op}, 1>(stag::VecArgs)"]
 
 
 def measured_traffic(kernel, links):
@@ -396,22 +402,24 @@ def batched_c4(stag, torch, synth):
 
 
 def c1_gpu(stag, torch, synth, solves=20):
-    """The 4^4 workload (Haar links, m = 0.1, 1e-10) on the GPU: the
-    one-workgroup solver in fp64 (Fig.1) and with fp32 inner iterations
-    (Sec.3.2), median over `solves` solves from b resident in HBM."""
+    """The 4^4 workload (Haar links, m = 0.1, 1e-10) on the GPU: plain fp64 CG
+    (Fig.1) in resident workgroups, and fp32 inner iterations (Sec.3.2) in one
+    workgroup, median over `solves` solves from b resident in HBM."""
     import statistics
     name = "c1_4x4x4x4"
     cfg = synth.CONFIGS[name]
     L, m, tol = cfg["L"], cfg["mass"], cfg["tol"]
     U, b = synth.config_links(name), synth.config_rhs(name)
-    out = {"lattice": list(L), "mass": m, "tol": tol, "solver": "one workgroup per right-hand side"}
+    out = {"lattice": list(L), "mass": m, "tol": tol}
     with stag.Context(0) as ctx:
         g = ctx.gauge(L, U, precisions=("f64", "f32"))
         fb = ctx.field(g, 0, "f64", 1).load(b)
         fx = ctx.field(g, 0, "f64", 1)
         for inner in ("f64", "f32"):
             p = stag.cg_params(tol=tol, inner=inner)
+            before = stag.stag_resident_counts(ctx)[0]
             stag.stag_cg_solve(ctx, g, [m], fb, fx, p)
+            resident = stag.stag_resident_counts(ctx)[0] > before
             ts = []
             for _ in range(solves):
                 torch.cuda.synchronize()
@@ -420,7 +428,8 @@ def c1_gpu(stag, torch, synth, solves=20):
                 torch.cuda.synchronize()
                 ts.append(time.perf_counter() - t0)
             out[inner] = {"time_to_1e-10_ms": round(statistics.median(ts) * 1e3, 3), "status": rc,
-                          "iters": st[0]["iters"], "true_rel_res": st[0]["true_rel_res"]}
+                          "iters": st[0]["iters"], "true_rel_res": st[0]["true_rel_res"],
+                          "solver": "resident workgroups" if resident else "one workgroup"}
     log("c1 4^4", out)
     return out
 
@@ -593,7 +602,7 @@ def main():
                          "profiles trace")
     ap.add_argument("--block-kernels-only", action="store_true",
                     help="only tune and time the block iteration kernels of the 24^3x48 workload "
-                         "for 4, 8 and 12 right-hand sides, then a 256 MiB copy kernel: the program "
+                         "of 4 and 8 right-hand sides, then a 256 MiB copy kernel: the program "
                          "the block-kernel profiles run")
     ap.add_argument("--c3-solves-only", action="store_true",
                     help="only the 32^3x64 Haar solves at m = 0.1 to 1e-8 (fp32 and fp16+scale "
@@ -675,7 +684,7 @@ def main():
             g = ctx.gauge(c4["L"], synth.config_links(name), precisions=("f64", "f32"), r12=True)
             out = {"block_kernels_only": True, "workload": name, "inner": "f32", "links": "r12",
                    "vh": g.vh, "tune": {}, "us": {}, "kernel_src_sha256": csrc_digest()}
-            for n in (4, 8, 12):
+            for n in (4, 8):  # the kernel sizes that blocks run in
                 out["tune"][n], _ = stag.stag_tune(ctx, g, "f32", n)
                 out["us"][n] = stag.stag_time_kernels(ctx, g, "f32", n, reps=20)
                 log("block kernels", n, out["tune"][n], out["us"][n])
@@ -715,7 +724,7 @@ def main():
             torch.mul(xs, 2.0, out=ys)  # reads and writes n * 4 bytes
         torch.cuda.synchronize()
         print(json.dumps({"kernels_only": True, "tune": tunes[inner], "us": us,
-                          "kernel_names": kernel_names(tunes[inner], inner),
+                          "kernel_names": kernel_names(tunes[inner], inner, r12),
                           "inner": inner, "links": "r12" if r12 else "full", "vh": vh,
                           "copy_bytes_read": n * 4, "copy_bytes_written": n * 4,
                           "kernel_src_sha256": csrc_digest()}), flush=True)
@@ -728,21 +737,25 @@ def main():
         rc, st = stag.stag_cg_solve(ctx, g, [mass], fb, fx, params)
         log("warmup", rc, st[0])
 
-    # ---- timed region: K whole solves (graph replays), b and x resident in HBM
+    # ---- timed region: K whole solves (their iterations inside the resident
+    # kernel), b and x resident in HBM
+    res0 = stag.stag_resident_counts(ctx)
     sec, last = timed_solves(stag, torch, ctx, g, mass, fb, fx, params, args.steps)
+    res1 = stag.stag_resident_counts(ctx)
+    resident = res1[0] - res0[0] == args.steps and res1[1] == res0[1]
     log("timed", args.steps, "solves:", round(sec * 1e3, 3), "ms each;", last)
 
-    # the same kernels inside a solve: one more solve with its kernels launched
-    # eagerly, events recorded at each kernel's start and end (the graph
-    # replays of the timed region cannot be bracketed kernel by kernel)
+    # the kernels of the kernel-per-stage solver (larger lattices, blocks, serving)
+    # on this system: one more solve with its kernels launched eagerly, events
+    # recorded at each kernel's start and end
     stag.stag_timing_enable(ctx, True)
     stag.stag_cg_solve(ctx, g, [mass], fb, fx, params)
     in_solve = {name: stag.stag_timing_read(ctx, kk) for name, kk in
                 (("hop_stage1", stag.K_HOP1), ("hop_stage2", stag.K_HOP2), ("update", stag.K_UPDATE))}
     stag.stag_timing_enable(ctx, False)
 
-    # ---- the iteration's kernels, launched exactly as in the solve and in its
-    # order, timed between HIP events on the library's stream
+    # ---- the iteration's kernels of the same solver, in its order, timed between
+    # HIP events on the library's stream
     us = stag.stag_time_kernels(ctx, g, inner, 1, reps=200)
     kinds = {}
     for k, name in enumerate(KERNEL_NAMES):
@@ -751,10 +764,12 @@ def main():
                        "GB/s": round(byts / (us[k] * 1e-6) / 1e9, 1)}
     dom = max(kinds, key=lambda k: kinds[k]["avg_us"])
     d = kinds[dom]
-    dom_name = kernel_names(tunes[inner], inner)[KERNEL_NAMES.index(dom)]
+    dom_name = kernel_names(tunes[inner], inner, r12)[KERNEL_NAMES.index(dom)]
     traffic = measured_traffic(dom_name, "r12" if r12 else "full")
     roofline = {"bound": "hbm", "achieved": d["GB/s"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(d["GB/s"] / HBM_PEAK_GBS, 4), "traffic": traffic,
+                "solver": "kernel per stage (its largest kernel on this system; the timed solves "
+                          + ("iterate in the resident kernel, see solve)" if resident else "run it)"),
                 "kernel_symbol": dom_name,
                 "kernel": (f"{dom} ({inner}, 16^3x32, {'12-parameter' if r12 else 'full'}"
                            f" links, S1={tunes[inner]['S1']} S2={tunes[inner]['S2']} "
@@ -804,7 +819,10 @@ def main():
         "roofline": roofline,
         "solve": {"iters": iters, "reliable_updates": last["reliable_updates"],
                   "true_rel_res": last["true_rel_res"], "time_to_1e-8_ms": round(sec * 1e3, 3),
+                  "iterations_in": "resident kernel" if resident else "kernel per stage",
                   "us_per_iteration": round(per_iter_us, 3),
+                  "bytes_per_iteration_GB/s": round(costs.cg_iteration_bytes_per_site(
+                      inner, True, r12=r12) * vh / (per_iter_us * 1e-6) / 1e9, 1),
                   "kernel_us_per_iteration": round(sum(us), 3),
                   "bytes_per_iteration": costs.cg_iteration_bytes_per_site(
                       inner, True, r12=r12) * vh},

@@ -8,8 +8,11 @@
 // dependent kernels of a graph it costs three launches, three fillings of the
 // chip with operands from cache, and each consumer's pass over the partials.
 // Here the links of both parities stay in registers for the whole launch (the
-// chip's register files hold 128 MiB), as do the own-site vectors, and an
-// iteration is two gathers and three waits:
+// chip's register files hold 128 MiB), as do the own-site vectors (two shapes of
+// full links do not fit and keep part in scratch memory: fp32 with one lane per
+// site 123 registers, 388 bytes a lane, fp64 with two 38 and 108; the first is
+// likely part of 16^3 x 32's 21.5 us an iteration against 14.1 with 12-parameter
+// links), and an iteration is two gathers and three waits:
 //   stage 1  gather d and r at the neighbours, t = D_oe (r + beta d) published;
 //   stage 2  gather t until it is there, A d, <d, A d>; exchange of the blocks'
 //            partials;

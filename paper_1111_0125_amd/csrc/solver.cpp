@@ -900,7 +900,7 @@ struct ResidentHold {
 // unit). Two lanes where they fit (8^4, us per iteration with 1 / 2 / 4 lanes: fp32
 // 8.7 / 8.0 / 10.0, fp64 - / 10.8 / 11.9, fp16 11.2 / 9.9 / 10.5; fewer blocks make
 // an exchange shorter, more lanes a wavefront's products); fp64 full links of
-// two pairs and both parities do not fit in registers, four lanes are faster
+// two pairs and both parities do not all fit in registers, four lanes are faster
 // until the blocks run out (12^4 13.0 against 14.4). One lane for the rest, where
 // the kernel per stage is still slower (16^3 x 32, us per iteration: fp32 22.5
 // against 14.1, full links 26.1 against 21.5, fp16 19.5 against 16.8).

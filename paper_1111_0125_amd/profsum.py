@@ -96,9 +96,15 @@ def read_trace(d):
 
 
 HOP = re.compile(r"stag::k_hop<(\d+), (\d+), (\d+), (\d+), (true|false), (\d+)>")
+# one right-hand side: k_hop1<prec, S, epilogue, pairs, r12, lazy, fin>
+HOP1 = re.compile(r"stag::k_hop1<(\d+), (\d+), (\d+), (\d+), (true|false), (true|false), (true|false)>")
 
 
 def hop_parts(name):
+    m = HOP1.search(name)
+    if m:
+        p, S, epi, npairs = (int(v) for v in m.groups()[:4])
+        return {"prec": p, "S": S, "N": 1, "epi": epi, "nt": True, "npairs": npairs}
     m = HOP.search(name)
     if not m:
         return None
@@ -118,7 +124,7 @@ def calibration(rows, copy_bytes, n_copy):
 
 
 PREC_NAME = {0: "f64", 1: "f32", 2: "f16s"}
-VEC = re.compile(r"stag::k_vec<(\d+), (\d+), (\d+)>")
+VEC = re.compile(r"stag::k_vec<(\d+), (\d+), (\d+), \d+>")
 
 
 def leg_attrs(leg):
@@ -218,8 +224,8 @@ def cmd_aapply(a):
               "then the fastest shape in three more runs of 3 + 50 applications (3 + 30 for the improved operator; the median run is reported), and at the end "
               "a 1 GiB elementwise copy (`torch.mul`, 3 + 20 launches). Every hop dispatch is "
               "attributed to its (leg, shape) by launch order, which the program prints; the two "
-              "hop kernels of each application are stage 1 (`k_hop<prec, S, 1, 0, nt, pairs>`, "
-              "D_oe) and stage 2 (`k_hop<prec, S, 1, 1, nt, pairs>`, D_eo with the m^2 update).", "",
+              "hop kernels of each application are stage 1 (`k_hop<prec, S, 1, 0, nt, pairs>` or "
+              "`k_hop1<prec, S, 0, ...>`, D_oe) and stage 2 (epilogue 1, D_eo with the m^2 update).", "",
               f"Calibration on the copy kernel (`{cname}`, {copy_bytes} bytes each way): FETCH_SIZE "
               f"reads {fkib:.1f} KiB per dispatch (scale {fs:.5f}), WRITE_SIZE {wkib:.1f} KiB "
               f"(scale {ws:.5f}).", ""]
@@ -285,10 +291,10 @@ def cmd_iteration(a):
             prec = PREC_NAME[h["prec"]]
             r12p = links == "r12"
             n = h["N"]
-            # blocks of 8 or more right-hand sides, and of several on lattices of
+            # blocks of 8 or more right-hand sides, and every solve on lattices of
             # 131072 sites per parity or more, form the direction in a pass of
             # their own: their hop stages read d as stored
-            lazy = n == 1 or (n < 8 and vh < 131072)
+            lazy = n < 8 and vh < 131072
             if h["epi"] == 0:
                 alg = vh * costs.hop_bytes_per_site(prec, 1, n, lazy=lazy, r12=r12p)
             elif h["epi"] == 2:
@@ -322,10 +328,11 @@ def cmd_iteration(a):
               "dispatches of each kernel symbol (the same work every launch). Template arguments: "
               "`k_hop<prec, S, N, epilogue, nt, pairs>` (prec 0 = f64, 1 = f32, 2 = f16s; S lanes "
               "per site; N right-hand sides; epilogue 0 = stage 1, 2 = stage 2 with <d, A d>), "
-              "`k_vec<prec, N, op>` (op 3 = mixed update, 2 = fp64 CG update). Compulsory bytes: "
-              "`paper_1111_0125_amd/costs.py` (blocks of several right-hand sides on this many "
-              "sites read the direction as stored; one right-hand side forms it in the hop "
-              "stages from r and the previous d).", "",
+              "`k_hop1<prec, S, epilogue, pairs, r12, lazy, fin>` (one right-hand side), "
+              "`k_vec<prec, N, op, runs>` (op 3 = mixed update, 2 = fp64 CG update). Compulsory bytes: "
+              "`paper_1111_0125_amd/costs.py` (blocks of 8, and every solve on 131072 sites per parity or "
+              "more, read the direction as stored; the others form it in the hop stages from r "
+              "and the previous d).", "",
               f"Calibration on the copy kernel (`{cname}`): FETCH_SIZE reads {fkib:.1f} KiB per "
               f"dispatch (scale {fs:.5f}), WRITE_SIZE {wkib:.1f} KiB (scale {ws:.5f}).", "",
               "HBM MB counts the bytes between L2 and the memory fabric (MALL or HBM); "
@@ -359,19 +366,20 @@ def cmd_headline(a):
     ev = bench["roofline"]["avg_us"]
     byts = bench["roofline"]["bytes_per_launch"]
     rows = [("timing loop (`stag_time_kernels`, last %d launches)" % a.reps, loop),
-            ("the solves' launches (warm-up and timed solves, HIP graphs; the eager solve)", solves),
-            (f"the solves' launches longer than {a.idle_us} us (active slot)", active)]
+            ("the eager solve's launches (`roofline.in_solve`)", solves),
+            (f"the eager solve's launches longer than {a.idle_us} us (active slot)", active)]
+    resident = [r for r in trace if "stag::k_persist" in r[1]]
     lines = [f"# rocprofv3 kernel trace: the dominant kernel of the {bench['config']['workload']}", "",
              "Commands (from the repository root on one MI355X; `<repo>` is that root), the "
              "unprofiled run first (it also writes the launch-shape table the profiled run then "
              "loads, so both run the same shapes and the trace has no autotuner sweep):", ""]
     lines += ["    " + c for c in a.cmd]
     lines += ["", f"Kernel: `{sym}` ({bench['roofline']['kernel']}), {byts} compulsory bytes per "
-              "launch. In the trace its launches are the warm-up and timed solves' (graph "
-              "replays; a launch whose slot is inactive, after a flag until its segment's fix-up "
-              "or after convergence, reads the state and exits), one more solve's launched "
-              "eagerly (`roofline.in_solve`), and last the 3 + 200 launches of "
-              "`stag_time_kernels` that `roofline` is computed from.", "",
+              "launch, of the kernel-per-stage solver. In the trace its launches are those of a "
+              "solve launched eagerly (`roofline.in_solve`; one whose slot is inactive, after a "
+              "flag until its segment's fix-up or after convergence, reads the state and exits), "
+              "and last the 3 + 200 launches of `stag_time_kernels` that `roofline` is computed "
+              "from. The warm-up and timed solves iterate in `k_persist` (below).", "",
               "| launches | count | mean us | median us | GB/s at the mean | frac of 8 TB/s |",
               "|---|---:|---:|---:|---:|---:|"]
     for label, d in rows:
@@ -380,6 +388,14 @@ def cmd_headline(a):
         m = statistics.mean(d)
         lines.append(f"| {label} | {len(d)} | {m:.3f} | {statistics.median(d):.3f} | "
                      f"{byts / (m * 1e-6) / 1e9:.1f} | {byts / (m * 1e-6) / 8e12:.4f} |")
+    if resident:
+        d = [r[2] for r in resident]
+        work = [v for v in d if v > 5.0]
+        lines += ["", f"`{resident[0][1]}` (the resident kernel, {bench['warmup']} warm-up and "
+                  f"{bench['steps']} timed solves of {bench['solve']['iters']} iterations): {len(d)} "
+                  f"launches, {len(work)} of them with iterations to do, {sum(work) / 1e3:.2f} ms, "
+                  f"{sum(work) / ((bench['warmup'] + bench['steps']) * bench['solve']['iters']):.2f} us per "
+                  f"iteration."]
     ins = bench["roofline"].get("in_solve")
     if ins:
         lines += ["", f"The unprofiled run's eager solve (`roofline.in_solve`): {ins['avg_us']} us per "
