@@ -157,6 +157,7 @@ struct stag_engine {
         hipEvent_t done = nullptr;
     };
     std::vector<Branch> gstreams;   // for the groups of a block, a set of the context's
+    bool gstreams_apart = false;    // they are known to run side by side
     hipEvent_t gfork = nullptr;
     stag::HopTune tune_lo, tune_64;
 };

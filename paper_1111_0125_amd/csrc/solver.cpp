@@ -67,9 +67,11 @@ void engine_destroy(stag_engine* e) {
         if (br.done) (void)hipEventDestroy(br.done);
         set.push_back(br.s);
     }
-    if (!set.empty()) {
+    if (e->gstreams_apart) {
         std::lock_guard<std::mutex> lk(ctx->branch_mu);
         ctx->branch_sets.push_back(set);
+    } else {
+        for (hipStream_t s : set) (void)hipStreamDestroy(s);
     }
     if (e->gfork) (void)hipEventDestroy(e->gfork);
     ctx->used.fetch_sub(e->bytes);
@@ -743,7 +745,7 @@ static int get_graph(EngineRun& R, int g0, int nk, int K, hipGraphExec_t* out) {
 
 // Streams on different hardware queues for the groups of a block: at most three
 // (8 + 4 + 1 of 13 right-hand sides). Sets are kept in the context; a new one costs
-// two to ten streams' creation and under 0.1 ms for each pair that is tried (0.3
+// three to eight streams' creation and under 0.1 ms for each pair that is tried (1
 // for one on the same queue).
 constexpr int kBranches = 3;
 constexpr int kBranchTries = 8;
@@ -754,6 +756,7 @@ static int take_branches(stag_engine* e, std::vector<hipStream_t>& set) {
     if (!ctx->branch_sets.empty()) {
         set = ctx->branch_sets.back();
         ctx->branch_sets.pop_back();
+        e->gstreams_apart = true;
         return STAG_OK;
     }
     hipError_t err = hipSuccess;
@@ -771,7 +774,9 @@ static int take_branches(stag_engine* e, std::vector<hipStream_t>& set) {
             if (apart && err == hipSuccess) err = streams_meet(q, s, ctx->meet, ++ctx->meet_token, &apart);
         (apart && err == hipSuccess ? set : spare).push_back(s);
     }
-    // none found for a place (a device with other work): any stream serves
+    // none found for a place (a device with other work): any stream serves, and
+    // the set is not kept
+    e->gstreams_apart = (int)set.size() == kBranches;
     while ((int)set.size() < kBranches && !spare.empty() && err == hipSuccess) {
         set.push_back(spare.back());
         spare.pop_back();

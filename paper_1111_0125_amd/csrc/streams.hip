@@ -18,9 +18,10 @@ static __global__ void k_meet(int* mine, const int* other, int* seen, int token,
 
 // One such kernel on a, then one on b: the first sees the second's flag only if b
 // does not wait behind a. dev: four ints; token: not used with them before. On
-// a busy device the second can be late (0.3 ms), and the answer is no.
+// a device with other work the second can be late (1 ms: a resident kernel of a
+// small lattice keeps its units for up to about that), and the answer is no.
 hipError_t streams_meet(hipStream_t a, hipStream_t b, int* dev, int token, bool* apart) {
-    constexpr long long limit = 30000;
+    constexpr long long limit = 100000;
     int seen = 0;
     hipLaunchKernelGGL(k_meet, dim3(1), dim3(1), 0, a, dev, dev + 1, dev + 2, token, limit);
     hipError_t e = hipGetLastError();

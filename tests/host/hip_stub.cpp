@@ -474,7 +474,7 @@ hipError_t launch_tiny_apply(int, int, const TinyApplyArgs&, hipStream_t s) {
 }
 
 hipError_t streams_meet(hipStream_t a, hipStream_t b, int*, int, bool* apart) {
-    *apart = stream_of(a)->queue != stream_of(b)->queue;
+    *apart = stream_of(a)->queue != stream_of(b)->queue && !ctl.never_apart;
     return hipSuccess;
 }
 

@@ -29,6 +29,7 @@ struct Control {
     std::atomic<int> persist_now{0}, persist_most{0};  // resident kernels running, and the most
     std::atomic<int> blocks_now{0}, blocks_most{0};  // their workgroups at one time
     std::atomic<int> paired_queues{0};       // streams 0 and 1, 2 and 3, ... share a hardware queue of four
+    std::atomic<int> never_apart{0};         // no two streams are found to run side by side
     std::atomic<unsigned> queues_used{0};    // by graph launches, a bit each
     std::atomic<int> persist_iters{0};               // the most iterations given to one launch
 };

@@ -435,7 +435,8 @@ static void bad_links() {
 }
 
 // The groups of a block run on streams of different hardware queues, whatever
-// streams the program created before.
+// streams the program created before; streams taken while none were found to are
+// not kept for the next gauge.
 static void groups_on_queues_of_their_own() {
     ctl.paired_queues = 1;
     for (int before = 0; before < 4; ++before)
@@ -452,6 +453,26 @@ static void groups_on_queues_of_their_own() {
                 s.small = 0;
                 CHECK(solve(c, g, s) == STAG_OK);
                 CHECK(__builtin_popcount(ctl.queues_used) == (n == 11 || n == 13 ? 3 : 2));
+                CHECK(stag_gauge_destroy(g) == STAG_OK);
+            }
+            stag_destroy(c);
+            CHECK(ctl.malloc_held == 0);
+        }
+    for (int before = 0; before < 4; ++before)
+        for (int n : {8, 13}) {
+            hipStream_t other = nullptr;
+            for (int k = 0; k < before; ++k) (void)hipStreamCreateWithFlags(&other, 0);
+            stag_ctx* c = nullptr;
+            CHECK(stag_create(0, 0, &c) == STAG_OK);
+            for (int busy : {1, 0}) {
+                ctl.never_apart = busy;
+                stag_gauge* g = make_gauge(c, k88, STAG_MASK_F64 | STAG_MASK_F32);
+                ctl.queues_used = 0;
+                Solve s;
+                s.n = n;
+                s.small = 0;
+                CHECK(solve(c, g, s) == STAG_OK);
+                CHECK(busy || __builtin_popcount(ctl.queues_used) == (n == 13 ? 3 : 2));
                 CHECK(stag_gauge_destroy(g) == STAG_OK);
             }
             stag_destroy(c);
