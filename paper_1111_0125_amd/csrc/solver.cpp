@@ -863,6 +863,7 @@ static int launch_block_graphs(EngineRun& R, int busy, int K) {
 // (33.1), 0.30 / 0.31 (33.9), 0.07 / 0.09 (55.6; in mixed CG the updates end launches
 // too); 8^3 x 16 fp64 with all of one XCD 0.06 / 14.7 (15.3), 0.06 / 0.61 (15.6), 0.07
 // / 0.08 (22.6); with 3/4 of each XCD 0.06 / 0.09 either way (15.4 and 15.8).
+// 6x10x8x16 fp32, one XCD full: its solve 14.24 / 14.65.
 constexpr int kPersistIters = 1024;
 constexpr int kPersistItersWide = 64;
 // Rounds (one launch and its fix-up) between polls.
